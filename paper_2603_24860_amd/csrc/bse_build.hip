@@ -340,6 +340,15 @@ template <int VEC> __device__ __forceinline__ void split_store(double2 x, double
   dim[c] = sg * x.y;
 }
 
+// 16 bytes from an address that is only element aligned.
+template <typename T, typename V16> __device__ __forceinline__ V16 load16(const T *p) {
+  typedef T Vu __attribute__((ext_vector_type(16 / sizeof(T)), aligned(sizeof(T))));
+  const Vu v = *reinterpret_cast<const Vu *>(p);
+  V16 r;
+  memcpy(&r, &v, 16);
+  return r;
+}
+
 // ---------------------------------------------------------------------------
 // direct term, fused: one workgroup per (q, KC consecutive k), all Nmb rows.
 //   stage 1  T^T[I][(k, t, vv')] = sum_J W_q[I][J] Re/Im(Mv(k, k-q)[vv'][J])
@@ -356,8 +365,19 @@ template <int VEC> __device__ __forceinline__ void split_store(double2 x, double
 // SEED: the workgroup takes its q and KC k points from a work list (one k per
 // pair-orbit representative, -1 for padding) and writes the blocks D of the
 // representatives to drep[orbit][cc'][vv'] instead of subtracting them from H.
-template <typename T, int MI, int KC, bool SEED, int NCB>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 3 : (MI >= 6 ? 1 : 2), 8))) void k_direct_fused(int n1, int n2, int n3, int nv, int nc,
+// RAG: nmb < 64 MI (any nmb in (64 (MI - 1), 64 MI)).  The rows of W past nmb
+// read row nmb - 1 and are dropped from the accumulators before stage 2, the
+// last slab of J and the last entries of Mc are read one by one from clamped
+// addresses and replaced by zero (selects, so that values past an array's row
+// never meet a product).  Rows are 4-byte (FP32 W) or 8-byte aligned only.
+// Bound by MFMA work like the padded shape; the work of the padding is the
+// rows of W (the slab loop ends at nmb).  Against the unfused pair of kernels
+// (T through memory, 128-wide tiles) at 13 x 13 x 1, 3 + 4 bands, Nmb = 150,
+// FP32: the whole build 1396 -> 678 us (24 -> 49 TFLOP/s), so every shape
+// whose rows fit (Nmb <= 384, nv <= 4, nc <= 6) takes the fused kernel and
+// the unfused pair keeps the larger ones.
+template <typename T, int MI, int KC, bool SEED, int NCB, bool RAG = false>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (RAG && MI >= 5 ? 2 : 3) : (MI >= 6 || (RAG && MI >= 5) ? 1 : 2), 8))) void k_direct_fused(int n1, int n2, int n3, int nv, int nc,
                                                      const int32_t *__restrict__ qorb,
                                                      const int32_t *__restrict__ pidx,
                                                      const uint8_t *__restrict__ pconj,
@@ -366,7 +386,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
                                                      const T *__restrict__ w, T *__restrict__ H,
                                                      int64_t ldh, double scale,
                                                      const int32_t *__restrict__ items,
-                                                     T *__restrict__ drep) {
+                                                     T *__restrict__ drep, int nmb_) {
   constexpr int BK = 16, P = Pitch<T, BK>::value;  // 16-deep slabs: two workgroups per CU
   constexpr int NMB = 64 * MI;             // rows of W handled by the workgroup
   constexpr int NI = 2 * KC;               // column blocks: (k, re/im)
@@ -390,7 +410,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   typedef typename Mfma<T>::frag_t frag_t;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int nk = n1 * n2 * n3, nvv = nv * nv, ncc = nc * nc;
-  const int nmb = NMB;
+  const int nmb = RAG ? nmb_ : NMB;
   const int32_t *item = SEED ? items + int64_t(blockIdx.x) * (1 + 2 * KC) : nullptr;
   const int q = SEED ? item[0] : int(blockIdx.y);
   const int k0 = blockIdx.x * KC;
@@ -432,10 +452,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   static_assert(RSTEP % 8 == 0, "the FP32 swizzle must repeat every RSTEP rows");
   const T *wrow0;
   int aoff0;
+  // RAG: only the rows of the last 64 may lie past nmb - 1 and are clamped
+  constexpr int NL = RAG ? 64 / RSTEP : 0;  // thread slots of those rows
+  static_assert(!RAG || NL * RSTEP == 64, "whole 64-row groups per slot range");
+  int wlast[RAG ? NL : 1];
   {
     const int row = tid / (BK / VEC), c = tid % (BK / VEC);
     wrow0 = wq + int64_t(row) * nmb + c * VEC;
     aoff0 = row * PP + swz(row, c) * VEC;
+    if constexpr (RAG) {
+#pragma unroll
+      for (int u = 0; u < NL; ++u) wlast[u] = (min(row + (NA - NL + u) * RSTEP, nmb - 1) - row) * nmb;
+    }
   }
   // a B row without data reads the first entries of mv (global memory, so
   // every load is a global one) and is zeroed by bmask
@@ -445,7 +473,10 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
 #pragma unroll
   for (int u = 0; u < NB; ++u) {
     const int it = tid + NT * u, row = it / BPR, c = it % BPR, kk = row / 16, vv = row % 16;
-    bsrc[u] = (brow[u] ? brow[u] : reinterpret_cast<const C2 *>(mv)) + (VEC == 4 ? 2 * c : c);
+    // (RAG: a row without data reads entry 0 only, mv may be shorter than a slab)
+    bsrc[u] = brow[u] || !RAG ? (brow[u] ? brow[u] : reinterpret_cast<const C2 *>(mv)) +
+                                    (VEC == 4 ? 2 * c : c)
+                              : reinterpret_cast<const C2 *>(mv);
     bstride[u] = brow[u] ? 1 : 0;
     bmask[u] = brow[u] ? T(1) : T(0);
     const int r0 = (2 * kk) * 16 + vv, r1 = r0 + 16;  // real and imaginary rows
@@ -462,13 +493,48 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   // registers and LDS and so workgroups per CU (measured: 0.47-0.50 of peak
   // against 0.68).
   const int r = lane & 15, g = lane >> 4;
+  // W row of slot u relative to wrow0 (RAG)
+  auto wofs = [&](int u) { return RAG && u >= NA - NL ? wlast[u - (NA - NL)] : u * RSTEP * nmb; };
   for (int j0 = 0; j0 < nmb; j0 += BK) {
     V16 ra[NA], rb[NB];
+    if (!RAG) {
 #pragma unroll
-    for (int u = 0; u < NA; ++u)
-      ra[u] = *reinterpret_cast<const V16 *>(wrow0 + int64_t(u) * RSTEP * NMB + j0);
+      for (int u = 0; u < NA; ++u)
+        ra[u] = *reinterpret_cast<const V16 *>(wrow0 + int64_t(u) * RSTEP * NMB + j0);
 #pragma unroll
-    for (int u = 0; u < NB; ++u) rb[u] = *reinterpret_cast<const V16 *>(bsrc[u] + bstride[u] * j0);
+      for (int u = 0; u < NB; ++u)
+        rb[u] = *reinterpret_cast<const V16 *>(bsrc[u] + bstride[u] * j0);
+    } else if (j0 + BK <= nmb) {  // whole slab: 16-byte loads, element aligned
+#pragma unroll
+      for (int u = 0; u < NA; ++u) ra[u] = load16<T, V16>(wrow0 + wofs(u) + j0);
+#pragma unroll
+      for (int u = 0; u < NB; ++u)
+        rb[u] = load16<T, V16>(reinterpret_cast<const T *>(bsrc[u] + bstride[u] * j0));
+    } else {  // the last, partial slab: entries past nmb - 1 read it and become zero
+#pragma unroll
+      for (int u = 0; u < NA; ++u) {
+        T e[VEC];
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+          const int J = j0 + (tid % (BK / VEC)) * VEC + i;
+          const T x = (wrow0 - (tid % (BK / VEC)) * VEC)[wofs(u) + min(J, nmb - 1)];
+          e[i] = J < nmb ? x : T(0);
+        }
+        memcpy(&ra[u], e, 16);
+      }
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        C2 e[VEC / 2];
+#pragma unroll
+        for (int i = 0; i < VEC / 2; ++i) {
+          const int J = j0 + ((tid + NT * u) % BPR) * (VEC / 2) + i;
+          const C2 *row = brow[u] ? brow[u] : reinterpret_cast<const C2 *>(mv);
+          const C2 x = row[brow[u] ? min(J, nmb - 1) : 0];
+          e[i] = C2{J < nmb ? x.x : T(0), J < nmb ? x.y : T(0)};
+        }
+        memcpy(&rb[u], e, 16);
+      }
+    }
 #pragma unroll
     for (int u = 0; u < NA; ++u) *reinterpret_cast<V16 *>(As + aoff0 + u * RSTEP * PP) = ra[u];
 #pragma unroll
@@ -508,6 +574,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   }
   // ---- stage 2 ----
   const int r16 = r;
+  if constexpr (RAG) {  // rows of T past nmb
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+      for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[mi][ni][j] = wm0 + 16 * mi + 4 * g + j < nmb ? acc[mi][ni][j] : T(0);
+  }
   const int ncb = (ncc + 15) / 16;
   C2 *red = reinterpret_cast<C2 *>(lds);  // [4][NCB*16][16]
   C2 *Hc = reinterpret_cast<C2 *>(H);
@@ -547,7 +622,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
           // four consecutive entries, 16-byte aligned (nmb and I0 multiples of 4)
           C2 m[4];
           const V16 *m16 = reinterpret_cast<const V16 *>(arowp + I0);
-          if constexpr (VEC == 4) {
+          if constexpr (RAG) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const C2 x = arowp[min(I0 + j, nmb - 1)];
+              m[j] = C2{I0 + j < nmb ? x.x : T(0), I0 + j < nmb ? x.y : T(0)};
+            }
+          } else if constexpr (VEC == 4) {
             const V16 a = m16[0], b = m16[1];
             m[0] = C2{T(a.x), T(a.y)};
             m[1] = C2{T(a.z), T(a.w)};
@@ -609,16 +690,23 @@ int32_t launch_fused(int MI, dim3 g, hipStream_t s, const bse_problem *p, void *
                      double scale, const int32_t *items = nullptr, void *drep = nullptr) {
   const int ncb = (p->nc * p->nc + 15) / 16;
   if (ncb < 1 || ncb > 3) return fail(BSE_EUNSUPPORTED, "fused direct kernel: nc^2 <= 48");
-#define BSE_FUSED_NCB(M, C)                                                                   \
-  BSE_LAUNCH(SEED ? "k_direct_seed" : "k_direct_fused", (k_direct_fused<T, M, KC, SEED, C>),  \
+  const bool rag = p->nmb % 64 != 0;
+  if (SEED && rag) return fail(BSE_EUNSUPPORTED, "seed construction needs Nmb = 64 m");
+#define BSE_FUSED_RAG(M, C, R)                                                                \
+  BSE_LAUNCH(SEED ? "k_direct_seed" : "k_direct_fused", (k_direct_fused<T, M, KC, SEED, C, R>), \
              g, dim3(NT), 0, s, p->grid[0], p->grid[1], p->grid[2], p->nv, p->nc, p->qorb,  \
              p->pidx, p->pconj, (const T *)p->mv, (const T *)p->mc, (const T *)p->w,        \
-             (T *)H, ldh, scale, items, (T *)drep)
+             (T *)H, ldh, scale, items, (T *)drep, p->nmb)
+#define BSE_FUSED_NCB(M, C)                                                                   \
+  {                                                                                         \
+    if (!SEED && rag) BSE_FUSED_RAG(M, C, !SEED);                                           \
+    else BSE_FUSED_RAG(M, C, false);                                                        \
+  }
 #define BSE_FUSED_CASE(M)                                                                     \
   case M:                                                                                   \
-    if (ncb == 1) BSE_FUSED_NCB(M, 1);                                                      \
-    else if (ncb == 2) BSE_FUSED_NCB(M, 2);                                                 \
-    else BSE_FUSED_NCB(M, 3);                                                               \
+    if (ncb == 1) BSE_FUSED_NCB(M, 1)                                                       \
+    else if (ncb == 2) BSE_FUSED_NCB(M, 2)                                                  \
+    else BSE_FUSED_NCB(M, 3)                                                               \
     break;
   switch (MI) {
     BSE_FUSED_CASE(1)
@@ -632,6 +720,7 @@ int32_t launch_fused(int MI, dim3 g, hipStream_t s, const bse_problem *p, void *
   }
 #undef BSE_FUSED_CASE
 #undef BSE_FUSED_NCB
+#undef BSE_FUSED_RAG
   BSE_HIP_CHECK(hipGetLastError());
   return BSE_OK;
 }
@@ -736,10 +825,12 @@ extern "C" int32_t bse_build(const bse_problem *p, int32_t prec, void *H, int64_
   const int64_t N = int64_t(nk) * p->nv * p->nc;
   if (!H) return fail(BSE_EINVAL, "H is NULL");
   if (ldh < N) return fail(BSE_ESHAPE, "ldh %lld < N %lld", (long long)ldh, (long long)N);
-  const bool fused = fused_ok(p);
+  // the workspace contract is by shape (bse_build_ws_min), also where the
+  // fused kernel's ragged form leaves the workspace unused
   const size_t pq = per_q_bytes(p, prec);
-  if (!fused && (!ws || ws_bytes < pq))
+  if (!fused_ok(p) && (!ws || ws_bytes < pq))
     return fail(BSE_EWORKSPACE, "workspace %zu bytes < %zu required", ws_bytes, pq);
+  const bool fused = p->nmb <= 384 && p->nv * p->nv <= 16 && p->nc * p->nc <= 48;
   const int qb = fused ? 1 : int(std::min<size_t>(nk, ws_bytes / pq));
   hipStream_t s = (hipStream_t)stream;
   const double inv_nk = 1.0 / nk;
@@ -754,7 +845,7 @@ extern "C" int32_t bse_build(const bse_problem *p, int32_t prec, void *H, int64_
     if (fused) {
       constexpr int KC = 2;  // k points per workgroup
       dim3 gf((unsigned)((nk + KC - 1) / KC), (unsigned)nk);
-      return launch_fused<T, KC>(p->nmb / 64, gf, s, p, H, ldh, inv_nk);
+      return launch_fused<T, KC>((p->nmb + 63) / 64, gf, s, p, H, ldh, inv_nk);
     }
     const int64_t M = 2 * int64_t(nk) * p->nv * p->nv;
     for (int q0 = 0; q0 < nk; q0 += qb) {
