@@ -350,9 +350,10 @@ template <typename T, typename V16> __device__ __forceinline__ V16 load16(const 
 }
 
 // ---------------------------------------------------------------------------
-// direct term, fused: one workgroup per (q, KC consecutive k), all Nmb rows.
+// direct term, fused: one workgroup per (q, kpw consecutive k), all Nmb rows,
+// KC = 2 column tiles of 16.
 //   stage 1  T^T[I][(k, t, vv')] = sum_J W_q[I][J] Re/Im(Mv(k, k-q)[vv'][J])
-//            wave w owns rows I in [w 16 MI, (w+1) 16 MI), all KC k's;
+//            wave w owns rows I in [w 16 MI, (w+1) 16 MI), all kpw k's;
 //   stage 2  D[cc'][vv'] = sum_I conj(Mc(k, k-q)[cc'][I]) T[vv'][I]
 //            straight from the accumulators: in the MFMA output layout lane
 //            (g, c) holds T^T rows 4g + j at column c, which is exactly the
@@ -362,6 +363,14 @@ template <typename T, typename V16> __device__ __forceinline__ V16 load16(const 
 // Requires nmb = 64 MI, nv^2 <= 16, nc^2 <= 16 NCB (NCB <= 3 row blocks of
 // stage 2, a template parameter so that unused accumulators take no registers).
 // ---------------------------------------------------------------------------
+// PACK (nv < 4, see fused_kpw, and every ragged shape): the nv^2 columns of consecutive k lie
+// side by side in the tiles, kpw up to 3, 8 or 32 k for nv = 3, 2, 1 instead of
+// one per tile, so that stage 1 does not multiply empty columns; a k whose
+// columns straddle both tiles takes two passes of stage 2.  17 x 17 x 1 with
+// 2 + 3 bands, Nmb = 192, FP32: 1903 -> 837 us; 13 x 13 x 1 with 3 + 4 bands,
+// Nmb = 150: 678 -> 562 us.  nv = 4 fills its tiles and keeps the fixed form
+// (its build at 8^3 measured 1 % slower with the loops over k).  kpw <= KC: one k
+// per tile, as without PACK.
 // SEED: the workgroup takes its q and KC k points from a work list (one k per
 // pair-orbit representative, -1 for padding) and writes the blocks D of the
 // representatives to drep[orbit][cc'][vv'] instead of subtracting them from H.
@@ -376,7 +385,7 @@ template <typename T, typename V16> __device__ __forceinline__ V16 load16(const 
 // FP32: the whole build 1396 -> 678 us (24 -> 49 TFLOP/s), so every shape
 // whose rows fit (Nmb <= 384, nv <= 4, nc <= 6) takes the fused kernel and
 // the unfused pair keeps the larger ones.
-template <typename T, int MI, int KC, bool SEED, int NCB, bool RAG = false>
+template <typename T, int MI, int KC, bool SEED, int NCB, bool RAG = false, bool PACK = RAG>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? (RAG && MI >= 5 ? 2 : 3) : (MI >= 6 || (RAG && MI >= 5) ? 1 : 2), 8))) void k_direct_fused(int n1, int n2, int n3, int nv, int nc,
                                                      const int32_t *__restrict__ qorb,
                                                      const int32_t *__restrict__ pidx,
@@ -386,7 +395,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
                                                      const T *__restrict__ w, T *__restrict__ H,
                                                      int64_t ldh, double scale,
                                                      const int32_t *__restrict__ items,
-                                                     T *__restrict__ drep, int nmb_) {
+                                                     T *__restrict__ drep, int nmb_, int kpw_) {
   constexpr int BK = 16, P = Pitch<T, BK>::value;  // 16-deep slabs: two workgroups per CU
   constexpr int NMB = 64 * MI;             // rows of W handled by the workgroup
   constexpr int NI = 2 * KC;               // column blocks: (k, re/im)
@@ -411,22 +420,24 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int nk = n1 * n2 * n3, nvv = nv * nv, ncc = nc * nc;
   const int nmb = RAG ? nmb_ : NMB;
+  const int kpw = PACK ? kpw_ : KC;             // k points of the workgroup
+  const int cpk = PACK && kpw > KC ? nvv : 16;  // columns from one k to the next
   const int32_t *item = SEED ? items + int64_t(blockIdx.x) * (1 + 2 * KC) : nullptr;
   const int q = SEED ? item[0] : int(blockIdx.y);
-  const int k0 = blockIdx.x * KC;
+  const int k0 = blockIdx.x * kpw;
   auto kof = [&](int kk) { return SEED ? item[1 + kk] : k0 + kk; };
   auto kok = [&](int k) { return SEED ? k >= 0 : k < nk; };
   const T *wq = w + int64_t(qorb[q]) * nmb * nmb;
-  // B-row sources: row = kk * 16 + vv' (re and im rows of one complex row)
+  // B-row sources: row = kk * cpk + vv' (re and im rows of one complex row)
   const C2 *brow[NB];
   T bsgn[NB];
 #pragma unroll
   for (int u = 0; u < NB; ++u) {
-    const int it = tid + NT * u, row = it / BPR, kk = row / 16, vv = row % 16;
-    const int k = kof(kk);
+    const int it = tid + NT * u, row = it / BPR, kk = row / cpk, vv = row % cpk;
+    const int k = kk < kpw ? kof(kk) : -1;
     brow[u] = nullptr;
     bsgn[u] = T(1);
-    if (kok(k) && vv < nvv) {
+    if (k >= 0 && kok(k) && vv < nvv) {
       const int kq = kminus(k, q, n1, n2, n3);
       const int64_t p = int64_t(k) * nk + kq;
       const bool cj = pconj[p] != 0;
@@ -472,7 +483,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
   T bmask[NB];
 #pragma unroll
   for (int u = 0; u < NB; ++u) {
-    const int it = tid + NT * u, row = it / BPR, c = it % BPR, kk = row / 16, vv = row % 16;
+    const int it = tid + NT * u, row = it / BPR, c = it % BPR, kk = row / 16, vv = row % 16;  // tile, column
     // (RAG: a row without data reads entry 0 only, mv may be shorter than a slab)
     bsrc[u] = brow[u] || !RAG ? (brow[u] ? brow[u] : reinterpret_cast<const C2 *>(mv)) +
                                     (VEC == 4 ? 2 * c : c)
@@ -595,9 +606,14 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
     const int cc = 16 * cb + Mfma<T>::arow(r16), c = cc / nc, c2 = cc % nc;
     mrow[cb] = cc < ncc ? ((c2 * nc + c) << 16) | (c * nc + c2) : -1;
   }
+  // column tile t holds columns 16 t .. 16 t + 15; one pass per k with columns
+  // there (D of that pass is valid in columns cl .. ch - 1 only)
 #pragma unroll
-  for (int kk = 0; kk < KC; ++kk) {
+  for (int t = 0; t < KC; ++t)
+  for (int kk = PACK ? 16 * t / cpk : t; kk <= (PACK ? min((16 * t + 15) / cpk, kpw - 1) : t); ++kk) {
     const int k = kof(kk);
+    const int cl = PACK ? max(kk * cpk - 16 * t, 0) : 0;
+    const int ch = PACK ? min(kk * cpk + nvv - 16 * t, 16) : nvv;
     acc_t dre[NCB], dim[NCB];
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb)
@@ -641,7 +657,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             const T are = am * m[j].x, aim = sgm * m[j].y;   // Mc = are + i aim
-            const T tre = acc[mi][2 * kk][j], tim = acc[mi][2 * kk + 1][j];
+            const T tre = acc[mi][2 * t][j], tim = acc[mi][2 * t + 1][j];
             // conj(Mc) T = (are tre + aim tim) + i (are tim - aim tre)
             dre[cb] = Mfma<T>::mma(are, tre, dre[cb]);
             dre[cb] = Mfma<T>::mma(aim, tim, dre[cb]);
@@ -659,17 +675,18 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
         red[(wv * NCB * 16 + 16 * cb + 4 * g + j) * 16 + r16] = C2{dre[cb][j], dim[cb][j]};
     __syncthreads();
     if (kok(k)) {
-      for (int e = tid; e < ncc * nvv; e += NT) {
-        const int cc = e / nvv, vv = e % nvv;
+      const int cw = ch - cl;
+      for (int e = tid; e < ncc * cw; e += NT) {
+        const int cc = e / cw, col = cl + e % cw, vv = 16 * t + col - kk * cpk;
         C2 sum = {T(0), T(0)};
 #pragma unroll
         for (int w4 = 0; w4 < 4; ++w4) {
-          const C2 x = red[(w4 * NCB * 16 + cc) * 16 + vv];
+          const C2 x = red[(w4 * NCB * 16 + cc) * 16 + col];
           sum.x += x.x;
           sum.y += x.y;
         }
         if (SEED) {
-          reinterpret_cast<C2 *>(drep)[int64_t(item[1 + KC + kk]) * ncc * nvv + e] = sum;
+          reinterpret_cast<C2 *>(drep)[(int64_t(item[1 + KC + kk]) * ncc + cc) * nvv + vv] = sum;
           continue;
         }
         const int c = cc / nc, c2 = cc % nc, v = vv / nv, v2 = vv % nv;
@@ -687,20 +704,22 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
 
 template <typename T, int KC, bool SEED = false>
 int32_t launch_fused(int MI, dim3 g, hipStream_t s, const bse_problem *p, void *H, int64_t ldh,
-                     double scale, const int32_t *items = nullptr, void *drep = nullptr) {
+                     double scale, int kpw, const int32_t *items = nullptr, void *drep = nullptr) {
   const int ncb = (p->nc * p->nc + 15) / 16;
   if (ncb < 1 || ncb > 3) return fail(BSE_EUNSUPPORTED, "fused direct kernel: nc^2 <= 48");
   const bool rag = p->nmb % 64 != 0;
   if (SEED && rag) return fail(BSE_EUNSUPPORTED, "seed construction needs Nmb = 64 m");
-#define BSE_FUSED_RAG(M, C, R)                                                                \
-  BSE_LAUNCH(SEED ? "k_direct_seed" : "k_direct_fused", (k_direct_fused<T, M, KC, SEED, C, R>), \
+#define BSE_FUSED_RAG(M, C, R, K)                                                             \
+  BSE_LAUNCH(SEED ? "k_direct_seed" : "k_direct_fused",                                     \
+             (k_direct_fused<T, M, KC, SEED, C, R, K>),                                     \
              g, dim3(NT), 0, s, p->grid[0], p->grid[1], p->grid[2], p->nv, p->nc, p->qorb,  \
              p->pidx, p->pconj, (const T *)p->mv, (const T *)p->mc, (const T *)p->w,        \
-             (T *)H, ldh, scale, items, (T *)drep, p->nmb)
+             (T *)H, ldh, scale, items, (T *)drep, p->nmb, kpw)
 #define BSE_FUSED_NCB(M, C)                                                                   \
   {                                                                                         \
-    if (!SEED && rag) BSE_FUSED_RAG(M, C, !SEED);                                           \
-    else BSE_FUSED_RAG(M, C, false);                                                        \
+    if (!SEED && rag) BSE_FUSED_RAG(M, C, !SEED, !SEED);                                    \
+    else if (!SEED && kpw > KC) BSE_FUSED_RAG(M, C, false, !SEED);                          \
+    else BSE_FUSED_RAG(M, C, false, false);                                                 \
   }
 #define BSE_FUSED_CASE(M)                                                                     \
   case M:                                                                                   \
@@ -758,6 +777,15 @@ __global__ __launch_bounds__(NT) void k_seed_assemble(int nk, int nv, int nc,
   double re = double(x.x) - scale * double(d.x), im = double(x.y) - scale * double(d.y);
   if (a == b) re += ec[int64_t(k) * nc + c] - ev[int64_t(k) * nv + v];
   reinterpret_cast<C2 *>(H)[a * ldh + b] = C2{T(re), T(im)};
+}
+
+// k points per workgroup of the fused direct kernel: as many as its KC tiles of
+// 16 columns hold (nv^2 columns each, side by side), but at least 2048
+// workgroups (eight per compute unit; 5^3 with one valence band, Nmb = 171,
+// FP64: 636 us against 698 us with at least 512), else one k per tile
+inline int fused_kpw(int nk, int nv, int KC) {
+  const int most = 16 * KC / (nv * nv), room = int(int64_t(nk) * nk / 2048);
+  return std::min(most, std::max(KC, room));
 }
 
 bool fused_ok(const bse_problem *p) { return fused_shape(p->nmb, p->nv, p->nc); }
@@ -843,9 +871,10 @@ extern "C" int32_t bse_build(const bse_problem *p, int32_t prec, void *H, int64_
                        (const T *)p->mx, p->vdiag, p->ev, p->ec, (T *)H, ldh, 2.0 * inv_nk, 1);
     BSE_HIP_CHECK(hipGetLastError());
     if (fused) {
-      constexpr int KC = 2;  // k points per workgroup
-      dim3 gf((unsigned)((nk + KC - 1) / KC), (unsigned)nk);
-      return launch_fused<T, KC>((p->nmb + 63) / 64, gf, s, p, H, ldh, inv_nk);
+      constexpr int KC = 2;  // column tiles per workgroup
+      const int kpw = fused_kpw(nk, p->nv, KC);
+      dim3 gf((unsigned)((nk + kpw - 1) / kpw), (unsigned)nk);
+      return launch_fused<T, KC>((p->nmb + 63) / 64, gf, s, p, H, ldh, inv_nk, kpw);
     }
     const int64_t M = 2 * int64_t(nk) * p->nv * p->nv;
     for (int q0 = 0; q0 < nk; q0 += qb) {
@@ -1038,7 +1067,7 @@ extern "C" int32_t bse_build_seed(int64_t plan, void *H, int64_t ldh, bse_stream
                2.0 * inv_nk, 0);
     BSE_HIP_CHECK(hipGetLastError());
     int32_t st = launch_fused<T, SEED_KC, true>(p->nmb / 64, dim3((unsigned)P.nitems), s, p,
-                                                nullptr, 0, 0.0, P.items, P.drep);
+                                                nullptr, 0, 0.0, SEED_KC, P.items, P.drep);
     if (st) return st;
     if (!H) return BSE_OK;  // pieces only (bse_project_seed reads them)
     dim3 ga((unsigned)(N * ((N + NT - 1) / NT)));

@@ -1,5 +1,5 @@
-"""The dense build at mixed-basis sizes that are no multiple of 64, against the
-FP64 oracle: every row count of the fused kernel's ragged form (one to six
+"""The dense build at mixed-basis sizes that are no multiple of 64 and with one
+to three valence bands, against the FP64 oracle: every row count of the fused kernel's ragged form (one to six
 64-row groups, one entry short of and past a group), one, two and three c c'
 row blocks, and the shapes the unfused kernels keep (more than 384 entries,
 five valence bands).
@@ -22,6 +22,9 @@ SHAPES = [  # (lattice, grid, nv, nc, nmb)
     ("hex", (5, 5, 1), 3, 4, 150), ("cubic", (2, 2, 2), 4, 4, 193), ("cubic", (2, 2, 2), 1, 6, 255),
     ("hex", (3, 3, 1), 4, 3, 257), ("cubic", (2, 2, 2), 2, 6, 319), ("cubic", (2, 2, 2), 3, 5, 321),
     ("hex", (3, 3, 1), 2, 2, 383), ("cubic", (2, 2, 2), 2, 3, 390), ("cubic", (2, 2, 2), 5, 2, 70),
+    # several k in one column tile: whole and partial groups of k, straddled tiles
+    ("cubic", (5, 5, 5), 1, 2, 64), ("hex", (7, 7, 1), 2, 5, 128), ("hex", (8, 8, 1), 3, 3, 192),
+    ("cubic", (4, 4, 4), 1, 3, 33),
 ]
 
 
