@@ -373,7 +373,8 @@ template <typename T, typename V16> __device__ __forceinline__ V16 load16(const 
 // per tile, as without PACK.
 // SEED: the workgroup takes its q and KC k points from a work list (one k per
 // pair-orbit representative, -1 for padding) and writes the blocks D of the
-// representatives to drep[orbit][cc'][vv'] instead of subtracting them from H.
+// representatives to drep[orbit][(v c)][(v' c')] instead of subtracting them
+// from H.
 // RAG: nmb < 64 MI (any nmb in (64 (MI - 1), 64 MI)).  The rows of W past nmb
 // read row nmb - 1 and are dropped from the accumulators before stage 2, the
 // last slab of J and the last entries of Mc are read one by one from clamped
@@ -685,11 +686,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) ==
           sum.x += x.x;
           sum.y += x.y;
         }
-        if (SEED) {
-          reinterpret_cast<C2 *>(drep)[(int64_t(item[1 + KC + kk]) * ncc + cc) * nvv + vv] = sum;
+        const int c = cc / nc, c2 = cc % nc, v = vv / nv, v2 = vv % nv;
+        if (SEED) {  // in the layout of H's (k, k') block: a row's nv nc entries together
+          const int nb = nv * nc;
+          reinterpret_cast<C2 *>(drep)[(int64_t(item[1 + KC + kk]) * nb + v * nc + c) * nb +
+                                       v2 * nc + c2] = sum;
           continue;
         }
-        const int c = cc / nc, c2 = cc % nc, v = vv / nv, v2 = vv % nv;
         const int64_t a = (int64_t(k) * nv + v) * nc + c;
         const int64_t b = (int64_t(kq) * nv + v2) * nc + c2;
         C2 hv = Hc[a * ldh + b];
@@ -747,7 +750,7 @@ int32_t launch_fused(int MI, dim3 g, hipStream_t s, const bse_problem *p, void *
 // ---------------------------------------------------------------------------
 // seed-mode assembly: every H element from the per-orbit pieces
 //   H[(k v c),(k' v' c')] = X[(o(k) v c),(o(k') v' c')] + delta (E_c - E_v)
-//                           - scale D[porb(k,k')][(c c')][(v v')]
+//                           - scale D[porb(k,k')][(v c)][(v' c')]
 // X: exchange between k-orbit representatives, D: direct blocks of the
 // pair-orbit representatives.  One row per workgroup row, columns coalesced.
 // ---------------------------------------------------------------------------
@@ -762,18 +765,18 @@ __global__ __launch_bounds__(NT) void k_seed_assemble(int nk, int nv, int nc,
                                                       T *__restrict__ H, int64_t ldh,
                                                       double scale) {
   typedef typename Cplx<T>::type C2;
-  const int nb = nv * nc, ncc = nc * nc, nvv = nv * nv;
+  const int nb = nv * nc;
   const int64_t N = int64_t(nk) * nb;
   const int64_t nbx = (N + NT - 1) / NT;  // workgroups per row
   const int64_t a = int64_t(blockIdx.x) / nbx;
   const int64_t b = (int64_t(blockIdx.x) % nbx) * NT + threadIdx.x;
   if (b >= N) return;
   const int k = int(a / nb), ia = int(a % nb), v = ia / nc, c = ia % nc;
-  const int k2 = int(b / nb), ib = int(b % nb), v2 = ib / nc, c2 = ib % nc;
+  const int k2 = int(b / nb), ib = int(b % nb);
   const C2 x = reinterpret_cast<const C2 *>(xs)[(int64_t(korb[k]) * nb + ia) * ldx +
                                                 int64_t(korb[k2]) * nb + ib];
   const int64_t o = porb[int64_t(k) * nk + k2];
-  const C2 d = reinterpret_cast<const C2 *>(drep)[(o * ncc + c * nc + c2) * nvv + v * nv + v2];
+  const C2 d = reinterpret_cast<const C2 *>(drep)[(o * nb + ia) * nb + ib];
   double re = double(x.x) - scale * double(d.x), im = double(x.y) - scale * double(d.y);
   if (a == b) re += ec[int64_t(k) * nc + c] - ev[int64_t(k) * nv + v];
   reinterpret_cast<C2 *>(H)[a * ldh + b] = C2{T(re), T(im)};

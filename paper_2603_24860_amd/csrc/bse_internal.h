@@ -62,7 +62,7 @@ int32_t build_bf16x3(const bse_problem *p, void *H, int64_t ldh, void *ws, size_
 
 // The seed pieces of a plan (bse_seed_plan; filled by bse_build_seed): the
 // exchange between k-orbit representatives xs [nkorb nb][ldx], the direct
-// blocks of the pair-orbit representatives drep [nporb][nc^2][nv^2], the
+// blocks of the pair-orbit representatives drep [nporb][nv nc][nv nc], the
 // k -> k-orbit and (k, k') -> pair-orbit maps; elements of the plan's
 // precision.  For projecting blocks straight from the pieces.
 struct SeedPieces {

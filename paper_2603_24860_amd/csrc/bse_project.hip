@@ -7,14 +7,20 @@
 //   H_mu[(O,j,v,c),(O',j',v',c')] =
 //       sum_{k in O, k' in O'} U_O[k,j] H[(k,v,c),(k',v',c')] U_O'[k',j'].
 //
-// Kernel k_project: one workgroup per (row band (v,c), column orbit O', row
-// orbit O).  The members of both orbits and both bases are staged in LDS once.
-// The H rows (k,v,c), k in O, restricted to the columns of O' (|O'| runs of
-// nv nc contiguous complex values) are fetched RU rows at a time, up to PCH
-// elements, with every load of a chunk issued before any is stored to LDS.
-// Each chunk is contracted with U_O' (thread = output column (j', v', c')) and
-// accumulated, times U_O[k, j], into registers.  Each H element is read exactly
-// once per projected block; the kernel is bound by HBM bandwidth.
+// Kernel k_project: one workgroup per (block, row bands (v,c), column orbit O',
+// row orbit O), all blocks of a call in one launch:
+//   stage 1  y_j[(k',b')] = sum_{k in O} U_O[k,j] H[(k,v,c),(k',b')]: a thread owns one
+//            column (k',b') and streams the rows k straight into registers, PU
+//            rows ahead; U_O comes through the scalar cache, so an element of H
+//            costs one load, its conversion and 2 r FMAs, and no LDS;
+//   stage 2  H_mu[j,(j',b')] = sum_{k' in O'} y_j[(k',b')] U_O'[k',j'], y staged in
+//            LDS PRG vectors at a time.
+// All sums in FP64.  Bound by the gathered reads of H (runs of nv nc entries).
+// The earlier form staged the rows of O' in LDS and multiplied by U_O' first
+// (2 r' LDS reads and conversions per element), one launch per block.  8^3 with
+// 4 + 4 bands, T1u (574 MB): 312 -> 182 us (3.1 TB/s); the six blocks of
+// 17 x 17 x 1 with 3 + 3 bands: 368 -> 116 us; the former block from seed
+// pieces: 537 -> 240 us.
 #include <hip/hip_runtime.h>
 
 #include <vector>
@@ -24,17 +30,34 @@
 namespace bse {
 namespace {
 
-constexpr int PNT = 256;
+constexpr int PNT = 256;     // threads per workgroup
 constexpr int PMAXR = 9;     // basis vectors per orbit: d_mu m_mu(O) <= d_max^2
-constexpr int PMAXCOL = 2;   // output columns per thread: r' nv nc <= 512
 constexpr int PMAXL = 48;    // orbit size <= |S|
-constexpr int PCH = 2048;    // H elements per chunk (8 per thread)
+constexpr int PMAXB = 12;    // blocks per launch
+// rows of H in flight per thread (FP32: 182 us with 8, 197 with 4, 205 with 12)
+template <typename T> constexpr int PU_OF = sizeof(T) == 4 ? 8 : 4;
+
+// One block of a launch (device pointers as in bse_block; Bmu may be NULL).
+struct ProjBlk {
+  const int32_t *mem_off, *members;
+  const int64_t *orb_off;
+  const int32_t *orb_dim;
+  const int64_t *ub_off;
+  const double *ub;
+  void *Hmu;
+  int64_t ldmu;
+  double2 *Bmu;
+};
+struct ProjList {
+  int n;
+  ProjBlk b[PMAXB];
+};
 
 // Source of the H elements when projecting straight from the seed pieces
 // (f1 without materialising H): every element is formed as the seed assembly
 // forms it,
 //   H[(k v c),(k' v' c')] = X[(o(k) v c),(o(k') v' c')] + delta (E_c - E_v)
-//                           - scale D[porb(k,k')][(c c')][(v v')],
+//                           - scale D[porb(k,k')][(v c)][(v' c')],
 // and rounded to T, so the projected block equals the projection of the
 // assembled H exactly.
 struct SeedSrc {
@@ -46,176 +69,272 @@ struct SeedSrc {
   double scale;
 };
 
-// PAIR (FP32 H, nv nc even): two entries per 16-byte load; a run of nv nc
-// entries starts at an even entry, so a pair never straddles two runs.
-template <typename T, bool SEEDSRC, int NCT, bool PAIR = false>
-__global__ __launch_bounds__(PNT) __attribute__((amdgpu_waves_per_eu(NCT == 1 && !SEEDSRC && sizeof(T) == 4 ? 6 : 1, 8))) void k_project(int nv, int nc, const T *__restrict__ H,
-                                                 int64_t ldh, const int32_t *__restrict__ mem_off,
-                                                 const int32_t *__restrict__ members,
-                                                 const int64_t *__restrict__ orb_off,
-                                                 const int32_t *__restrict__ orb_dim,
-                                                 const int64_t *__restrict__ ub_off,
-                                                 const double *__restrict__ ub, T *__restrict__ Hmu,
-                                                 int64_t ldmu, SeedSrc sd) {
-  typedef typename std::conditional<sizeof(T) == 4, float2, double2>::type C2;
-  __shared__ C2 rows[PCH];
-  __shared__ double u1s[PMAXL * PMAXR], u2s[PMAXL * PMAXR];
-  __shared__ int32_t m1s[PMAXL], m2s[PMAXL];
-  __shared__ int32_t o1s[SEEDSRC ? PMAXL : 1], o2s[SEEDSRC ? PMAXL : 1];  // k orbits of the members
-  __shared__ int32_t pps[SEEDSRC ? PMAXL * PMAXL : 1];  // pair orbits of the member pairs
-  const int nb = nv * nc;
-  const int band = blockIdx.x;        // (v, c) of the output rows
-  // orbit ids grow with orbit size on the simple grids, so the largest (longest)
-  // orbit pairs are dispatched first and do not form a tail
-  const int o2 = gridDim.y - 1 - blockIdx.y, o1 = gridDim.z - 1 - blockIdx.z;
-  const int r1 = orb_dim[o1], r2 = orb_dim[o2];
-  if (r1 == 0 || r2 == 0) return;
-  const int L1 = mem_off[o1 + 1] - mem_off[o1], L2 = mem_off[o2 + 1] - mem_off[o2];
-  // orbits have at most |S| members and bases at most d_mu^2 vectors (the
-  // host checks PMAXL nb <= PCH); anything else is not a valid block
-  if (L1 > PMAXL || L2 > PMAXL || r1 > PMAXR || r2 > PMAXR) return;
-  const int32_t *m1 = members + mem_off[o1], *m2 = members + mem_off[o2];
-  for (int i = threadIdx.x; i < L1 * r1; i += PNT) u1s[i] = ub[ub_off[o1] + i];
-  for (int i = threadIdx.x; i < L2 * r2; i += PNT) u2s[i] = ub[ub_off[o2] + i];
-  if (threadIdx.x < L2) m2s[threadIdx.x] = m2[threadIdx.x];
-  if (threadIdx.x < L1) m1s[threadIdx.x] = m1[threadIdx.x];
-  if constexpr (SEEDSRC) {
-    if (threadIdx.x < L2) o2s[threadIdx.x] = sd.korb[m2[threadIdx.x]];
-    if (threadIdx.x < L1) o1s[threadIdx.x] = sd.korb[m1[threadIdx.x]];
-    for (int q = threadIdx.x; q < L1 * L2; q += PNT)
-      pps[q] = sd.porb[int64_t(m1[q / L2]) * sd.nk + m2[q % L2]];
-  }
-  const int ncol = r2 * nb, per = L2 * nb;
-  const int RU = PCH / per;  // rows per chunk (>= 1)
-  double accr[NCT][PMAXR], acci[NCT][PMAXR];  // NCT output columns per thread
-#pragma unroll
-  for (int t = 0; t < NCT; ++t)
-#pragma unroll
-    for (int j = 0; j < PMAXR; ++j) accr[t][j] = acci[t][j] = 0.0;
-  const int v = band / nc, c = band % nc;
-  __syncthreads();  // m1s, m2s
-  // chunk loads go to registers; the next chunk's loads are in flight while
-  // the current one is contracted from LDS
-  static_assert(!PAIR || (sizeof(T) == 4 && !SEEDSRC), "pairs: FP32 H only");
-  constexpr int NL = PAIR ? PCH / (2 * PNT) : PCH / PNT;  // loads per thread and chunk
-  typedef typename std::conditional<PAIR, float4, C2>::type LV;
-  LV x[NL];
-  // every load is issued unconditionally from a clamped, in-bounds index and
-  // entries past the chunk are zeroed afterwards, so the loads do not wait on
-  // one another
-  auto fetch = [&](int i0) {
-    const int nr = std::min(RU, L1 - i0);
-    if constexpr (PAIR) {
-#pragma unroll
-      for (int u = 0; u < NL; ++u) {
-        const int q = threadIdx.x + PNT * u;
-        const int e = std::min(2 * q, nr * per - 2);
-        const int ii = e / per, rem = e - ii * per, i2 = rem / nb, b2 = rem - i2 * nb;
-        const int64_t a = (int64_t(m1s[i0 + ii]) * nv + v) * nc + c;
-        x[u] = *reinterpret_cast<const float4 *>(reinterpret_cast<const C2 *>(H) + a * ldh +
-                                                 int64_t(m2s[i2]) * nb + b2);
-      }
-#pragma unroll
-      for (int u = 0; u < NL; ++u)
-        if (2 * (threadIdx.x + PNT * u) >= nr * per) x[u] = LV{0, 0, 0, 0};
-      return;
-    } else {
-#pragma unroll
-    for (int u = 0; u < PCH / PNT; ++u) {
-      const int e0 = threadIdx.x + PNT * u;
-      const int e = std::min(e0, nr * per - 1);
-      const int ii = e / per, rem = e - ii * per, i2 = rem / nb, b2 = rem - i2 * nb;
-      if constexpr (SEEDSRC) {
-        const int k = m1s[i0 + ii], k2 = m2s[i2], ia = v * nc + c;
-        const int v2 = b2 / nc, c2 = b2 % nc;
-        const C2 xe = reinterpret_cast<const C2 *>(sd.xs)[(int64_t(o1s[i0 + ii]) * nb + ia) * sd.ldx +
-                                                          int64_t(o2s[i2]) * nb + b2];
-        const int64_t o = pps[(i0 + ii) * L2 + i2];
-        const C2 d = reinterpret_cast<const C2 *>(sd.drep)[(o * (nc * nc) + c * nc + c2) * (nv * nv) +
-                                                           v * nv + v2];
-        double re = double(xe.x) - sd.scale * double(d.x), im = double(xe.y) - sd.scale * double(d.y);
-        if (k == k2 && ia == b2) re += sd.ec[int64_t(k) * nc + c] - sd.ev[int64_t(k) * nv + v];
-        x[u] = C2{T(re), T(im)};
-      } else {
-        const int64_t a = (int64_t(m1s[i0 + ii]) * nv + v) * nc + c;
-        x[u] = reinterpret_cast<const C2 *>(H)[a * ldh + int64_t(m2s[i2]) * nb + b2];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < PCH / PNT; ++u)
-      if (threadIdx.x + PNT * u >= nr * per) x[u] = C2{0, 0};
-    }
-  };
-  fetch(0);
-  for (int i0 = 0; i0 < L1; i0 += RU) {
-    const int nr = std::min(RU, L1 - i0);
-    __syncthreads();  // the previous chunk has been consumed
-#pragma unroll
-    for (int u = 0; u < NL; ++u) {
-      if constexpr (PAIR)
-        reinterpret_cast<float4 *>(rows)[threadIdx.x + PNT * u] = x[u];
-      else
-        rows[threadIdx.x + PNT * u] = x[u];
-    }
-    __syncthreads();
-    if (i0 + RU < L1) fetch(i0 + RU);
-#pragma unroll
-    for (int t = 0; t < NCT; ++t) {
-      const int col = threadIdx.x + PNT * t;
-      if (col >= ncol) break;
-      const int j2 = col / nb, b2 = col % nb;
-      for (int ii = 0; ii < nr; ++ii) {
-        double zr = 0, zi = 0;
-        for (int i2 = 0; i2 < L2; ++i2) {
-          const C2 h = rows[ii * per + i2 * nb + b2];
-          const double u = u2s[i2 * r2 + j2];
-          zr += u * double(h.x);
-          zi += u * double(h.y);
-        }
-#pragma unroll
-        for (int j = 0; j < PMAXR; ++j)
-          if (j < r1) {
-            const double u = u1s[(i0 + ii) * r1 + j];
-            accr[t][j] += u * zr;
-            acci[t][j] += u * zi;
-          }
-      }
-    }
-  }
-  const int64_t rbase = orb_off[o1] + band, cbase = orb_off[o2];
-#pragma unroll
-  for (int t = 0; t < NCT; ++t) {
-    const int col = threadIdx.x + PNT * t;
-    if (col >= ncol) break;
-#pragma unroll
-    for (int j = 0; j < PMAXR; ++j)
-      if (j < r1)
-        reinterpret_cast<C2 *>(Hmu)[(rbase + int64_t(j) * nb) * ldmu + cbase + col] =
-            C2{T(accr[t][j]), T(acci[t][j])};
-  }
-}
-
-// B_mu[(O,j,b)] = sum_{k in O} U_O[k,j] B[(k,b)]; one thread per output element.
-__global__ void k_project_vec(int nkorb, int nb, const int32_t *__restrict__ mem_off,
-                              const int32_t *__restrict__ members,
-                              const int64_t *__restrict__ orb_off,
-                              const int32_t *__restrict__ orb_dim,
-                              const int64_t *__restrict__ ub_off, const double *__restrict__ ub,
-                              const double2 *__restrict__ B, double2 *__restrict__ Bmu) {
-  const int o = blockIdx.x;
-  const int r = orb_dim[o], L = mem_off[o + 1] - mem_off[o];
-  const int32_t *m = members + mem_off[o];
-  const double *U = ub + ub_off[o];
+// B_mu[(O,j,b)] = sum_{k in O} U_O[k,j] B[(k,b)] for one orbit of one block; one
+// output element per thread, the members' loads four at a time.
+__device__ __forceinline__ void project_vec(const ProjBlk &K, int o, int nb,
+                                            const double2 *__restrict__ B) {
+  const int r = K.orb_dim[o], L = K.mem_off[o + 1] - K.mem_off[o];
+  const int32_t *m = K.members + K.mem_off[o];
+  const double *U = K.ub + K.ub_off[o];
   for (int e = threadIdx.x; e < r * nb; e += blockDim.x) {
     const int j = e / nb, b = e % nb;
     double sr = 0, si = 0;
-    for (int i = 0; i < L; ++i) {
-      const double2 x = B[int64_t(m[i]) * nb + b];
-      sr += U[i * r + j] * x.x;
-      si += U[i * r + j] * x.y;
+    for (int i = 0; i < L; i += 4) {
+      double2 x[4];
+      double u[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {  // members past the last read it and are dropped
+        const int ii = std::min(i + q, L - 1);
+        x[q] = B[int64_t(m[ii]) * nb + b];
+        u[q] = U[ii * r + j];
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (i + q < L) {
+          sr += u[q] * x[q].x;
+          si += u[q] * x[q].y;
+        }
     }
-    Bmu[orb_off[o] + e] = double2{sr, si};
+    K.Bmu[K.orb_off[o] + e] = double2{sr, si};
   }
+}
+
+// A row of a basis, read through the scalar cache (the address is the same for
+// every lane, the bases are never written by a kernel of this file).
+typedef const __attribute__((address_space(4))) double *ConstD;
+// A value that is the same for every lane, in a scalar register.
+__device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ int64_t uni(int64_t x) {
+  const unsigned lo = __builtin_amdgcn_readfirstlane(int(x));
+  const unsigned hi = __builtin_amdgcn_readfirstlane(int(x >> 32));
+  return int64_t(uint64_t(hi) << 32 | lo);
+}
+
+// One column (k',b') of the rows (k,v,c), k in O, as the kernel reads it: load()
+// fetches what row i needs, value() gives the element.  From H, or formed from
+// the seed pieces: the exchange entry depends on the orbits alone, so where
+// every member of O has the same k orbit (ONEX, any basis of this library) it
+// is loaded once per column; the diagonal term only where O is O' (diag).
+template <typename T, bool SEEDSRC, bool ONEX> struct ProjSrc {
+  typedef typename std::conditional<sizeof(T) == 4, float2, double2>::type C2;
+  struct Raw {
+    C2 a;
+  };
+  const C2 *col;
+  int64_t stride;  // of k
+  const int32_t *m1s;
+  __device__ __forceinline__ Raw load(int i) const { return {col[int64_t(uni(m1s[i])) * stride]}; }
+  __device__ __forceinline__ C2 value(const SeedSrc &, Raw r, int) const { return r.a; }
+};
+template <typename T, bool ONEX> struct ProjSrc<T, true, ONEX> {
+  typedef typename std::conditional<sizeof(T) == 4, float2, double2>::type C2;
+  struct Raw {
+    C2 d, x;
+  };
+  const C2 *xcol, *dcol;  // xs of column (O', b') and drep at (band, b')
+  int64_t xstride;        // xs elements of a k orbit
+  int dstride;            // drep elements of a pair orbit
+  C2 x0;                  // ONEX: the exchange entry
+  const int32_t *m1s, *o1s, *pp;  // pair orbits (member i, this column's member)
+  int L2, kdiag;          // k' where the column holds the diagonal entry of row k', else -1
+  int nv, nc, band;
+  __device__ __forceinline__ Raw load(int i) const {
+    Raw r;
+    r.d = dcol[int64_t(pp[i * L2]) * dstride];
+    if constexpr (!ONEX) r.x = xcol[int64_t(o1s[i]) * xstride];
+    return r;
+  }
+  __device__ __forceinline__ C2 value(const SeedSrc &sd, Raw r, int i) const {
+    const C2 xe = ONEX ? x0 : r.x, d = r.d;
+    double re = double(xe.x) - sd.scale * double(d.x), im = double(xe.y) - sd.scale * double(d.y);
+    const int k = m1s[i];
+    if (k == kdiag) re += sd.ec[int64_t(k) * nc + band % nc] - sd.ev[int64_t(k) * nv + band / nc];
+    return C2{T(re), T(im)};
+  }
+};
+
+// Stage 1 for one column: y[j] = sum_i U[i][j] h_i, PU rows in flight.  R is the
+// number of basis vectors r1, or (GEN) an upper bound of it: the entries past
+// r1 - 1 then read that one, and their sums are not used.
+template <typename T, int R, bool GEN, typename Src>
+__device__ __forceinline__ void proj_stage1(const Src &S, const SeedSrc &sd, ConstD u1, int r1,
+                                            int L1, bool work, double2 (&y)[PMAXR]) {
+  constexpr int PU = PU_OF<T>;
+  double ar[R], ai[R];
+#pragma unroll
+  for (int j = 0; j < R; ++j) ar[j] = ai[j] = 0.0;
+  if (work) {
+    typename Src::Raw x[PU];
+#pragma unroll
+    for (int u = 0; u < PU; ++u) x[u] = S.load(std::min(u, L1 - 1));
+    for (int i0 = 0; i0 < L1; i0 += PU) {
+      typename Src::Raw xc[PU];
+#pragma unroll
+      for (int u = 0; u < PU; ++u) xc[u] = x[u];
+      if (i0 + PU < L1)
+#pragma unroll
+        for (int u = 0; u < PU; ++u) x[u] = S.load(std::min(i0 + PU + u, L1 - 1));
+#pragma unroll
+      for (int u = 0; u < PU; ++u) {
+        if (i0 + u >= L1) break;
+        const auto h = S.value(sd, xc[u], i0 + u);
+        const double hr = double(h.x), hi = double(h.y);
+        double w[R];
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+          w[j] = u1[GEN ? (i0 + u) * r1 + std::min(j, r1 - 1) : (i0 + u) * R + j];
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+          ar[j] += w[j] * hr;
+          ai[j] += w[j] * hi;
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < R; ++j) y[j] = double2{ar[j], ai[j]};
+}
+// the sizes of isotypic and partner bases, else a bound
+#define BSE_PROJ_S1                                                              \
+  switch (r1) {                                                                  \
+    case 1: proj_stage1<T, 1, false>(S, sd, u1, r1, L1, work, y); break;         \
+    case 2: proj_stage1<T, 2, false>(S, sd, u1, r1, L1, work, y); break;         \
+    case 3: proj_stage1<T, 3, false>(S, sd, u1, r1, L1, work, y); break;         \
+    case 4: proj_stage1<T, 4, false>(S, sd, u1, r1, L1, work, y); break;         \
+    case 6: proj_stage1<T, 6, false>(S, sd, u1, r1, L1, work, y); break;         \
+    case 9: proj_stage1<T, 9, false>(S, sd, u1, r1, L1, work, y); break;         \
+    default: proj_stage1<T, 9, true>(S, sd, u1, r1, L1, work, y);                \
+  }
+
+// outs (dynamic LDS): [r1][r2 nb] sums over the column tiles, where there are several.
+constexpr int PRG = 3;  // vectors of y staged at a time (9: 271 us instead of 182)
+template <typename T, bool SEEDSRC>
+__global__ __launch_bounds__(PNT) void k_project(int nv, int nc, const T *__restrict__ H,
+                                                    int64_t ldh, ProjList P, SeedSrc sd,
+                                                    const double2 *__restrict__ B, int bpw) {
+  typedef typename std::conditional<sizeof(T) == 4, float2, double2>::type C2;
+  extern __shared__ __attribute__((aligned(16))) unsigned char plds[];
+  __shared__ double2 ys[PRG * PNT];
+  __shared__ double u2s[PMAXL * PMAXR];
+  __shared__ int32_t m1s[PMAXL], m2s[PMAXL];
+  __shared__ int32_t o1s[SEEDSRC ? PMAXL : 1], o2s[SEEDSRC ? PMAXL : 1];  // k orbits of the members
+  __shared__ int32_t pps[SEEDSRC ? PMAXL * PMAXL : 1];  // pair orbits of the member pairs
+  constexpr int nt = PNT;
+  const int tid = threadIdx.x, nb = nv * nc;
+  double2 *outs = reinterpret_cast<double2 *>(plds);
+  const ProjBlk &K = P.b[blockIdx.x % P.n];
+  const int band0 = int(blockIdx.x / P.n) * bpw;  // first (v, c) of the output rows
+  // orbit ids grow with orbit size on the simple grids, so the largest (longest)
+  // orbit pairs are dispatched first and do not form a tail
+  const int o2 = gridDim.y - 1 - blockIdx.y, o1 = gridDim.z - 1 - blockIdx.z;
+  if (K.Bmu && band0 == 0 && o1 == o2) project_vec(K, o1, nb, B);
+  const int r1 = uni(K.orb_dim[o1]), r2 = uni(K.orb_dim[o2]);
+  const int a1 = uni(K.mem_off[o1]), a2 = uni(K.mem_off[o2]);
+  const int L1 = uni(K.mem_off[o1 + 1]) - a1, L2 = uni(K.mem_off[o2 + 1]) - a2;
+  const int64_t v1 = uni(K.ub_off[o1]), v2 = uni(K.ub_off[o2]);
+  const int64_t q1 = uni(K.orb_off[o1]), q2 = uni(K.orb_off[o2]);
+  if (r1 == 0 || r2 == 0) return;
+  // orbits have at most |S| members and bases at most d_mu^2 vectors; anything
+  // else is not a valid block
+  if (L1 > PMAXL || L2 > PMAXL || r1 > PMAXR || r2 > PMAXR) return;
+  const int32_t *m1 = K.members + a1, *m2 = K.members + a2;
+  if (tid < L2) m2s[tid] = m2[tid];
+  if (tid < L1) m1s[tid] = m1[tid];
+  for (int i = tid; i < L2 * r2; i += nt) u2s[i] = K.ub[v2 + i];
+  bool onex = false;
+  if constexpr (SEEDSRC) {
+    if (tid < L2) o2s[tid] = sd.korb[m2[tid]];
+    if (tid < L1) o1s[tid] = sd.korb[m1[tid]];
+    for (int q = tid; q < L1 * L2; q += nt)
+      pps[q] = sd.porb[int64_t(m1[q / L2]) * sd.nk + m2[q % L2]];
+    onex = tid >= L1 || sd.korb[m1[tid]] == sd.korb[m1[0]];
+  }
+  if constexpr (SEEDSRC)
+    onex = __syncthreads_and(onex);
+  else
+    __syncthreads();
+  const ConstD u1 = (ConstD)(uintptr_t)(K.ub + v1);
+  const int per = L2 * nb, oc = r2 * nb;
+  // columns go to the threads in whole waves; where they take at most half of
+  // them, several bands run side by side (a wave has one band)
+  const int pad = std::min(nt, (per + 63) / 64 * 64), bc = nt / pad;
+  const int bend = std::min(band0 + bpw, nb), bl = uni(tid / pad), ct = tid % pad;
+  for (int bb = band0; bb < bend; bb += bc) {
+    const int nbd = std::min(bc, bend - bb);  // bands of this round
+    const int band = std::min(bb + bl, bend - 1);
+    for (int t0 = 0; t0 < per; t0 += nt) {
+      const int col = t0 + ct, cc = std::min(col, per - 1), i2 = cc / nb, b2 = cc % nb;
+      const bool work = col < per && bl < nbd;
+      double2 y[PMAXR];
+      if constexpr (SEEDSRC) {
+        const C2 *xcol = reinterpret_cast<const C2 *>(sd.xs) + int64_t(band) * sd.ldx +
+                         int64_t(o2s[i2]) * nb + b2;
+        const C2 *dcol = reinterpret_cast<const C2 *>(sd.drep) + band * nb + b2;
+        const int kdiag = o1 == o2 && band == b2 ? m2s[i2] : -1;
+        const C2 x0 = xcol[int64_t(o1s[0]) * nb * sd.ldx];
+        if (onex) {
+          const ProjSrc<T, true, true> S{xcol, dcol, nb * sd.ldx, nb * nb, x0,   m1s, o1s,
+                                         pps + i2, L2, kdiag, nv, nc, band};
+          BSE_PROJ_S1
+        } else {
+          const ProjSrc<T, true, false> S{xcol, dcol, nb * sd.ldx, nb * nb, x0,   m1s, o1s,
+                                          pps + i2, L2, kdiag, nv, nc, band};
+          BSE_PROJ_S1
+        }
+      } else {
+        const ProjSrc<T, false, false> S{
+            reinterpret_cast<const C2 *>(H) + band * ldh + int64_t(m2s[i2]) * nb + b2, nb * ldh, m1s};
+        BSE_PROJ_S1
+      }
+      // ---- stage 2, PRG vectors at a time ----
+      const int cn = std::min(nt, per - t0);  // columns of this tile
+      const bool last = t0 + nt >= per, tiled = per > nt;  // (tiled: one band at a time)
+#pragma unroll
+      for (int g = 0; g < PMAXR; g += PRG) {
+        if (g >= r1) break;
+        __syncthreads();  // ys of the previous vectors has been read
+        if (work)
+#pragma unroll
+          for (int q = 0; q < PRG; ++q) ys[q * nt + tid] = y[g + q];
+        __syncthreads();
+        const int nq = std::min(PRG, r1 - g);
+        for (int e = tid; e < nbd * nq * oc; e += nt) {
+          const int f = e % oc, qb = e / oc, q = qb % nq, eb = qb / nq, j2 = f / nb, bq = f % nb;
+          double zr = 0, zi = 0;
+          // members whose entry (k', bq) lies in this tile
+          const int ia = t0 > bq ? (t0 - bq + nb - 1) / nb : 0;
+          const int ib = std::min(L2, (t0 + cn - bq + nb - 1) / nb);
+          const double2 *yp = ys + q * nt + eb * pad + bq - t0;
+#pragma unroll 4
+          for (int k2 = ia; k2 < ib; ++k2) {
+            const double2 yv = yp[k2 * nb];
+            const double w = u2s[k2 * r2 + j2];
+            zr += w * yv.x;
+            zi += w * yv.y;
+          }
+          if (tiled) {
+            double2 &z = outs[(g + q) * oc + f];
+            if (t0 > 0) {
+              zr += z.x;
+              zi += z.y;
+            }
+            z = double2{zr, zi};
+          }
+          if (last)
+            reinterpret_cast<C2 *>(K.Hmu)[(q1 + bb + eb + int64_t(g + q) * nb) * K.ldmu + q2 + f] =
+                C2{T(zr), T(zi)};
+        }
+      }
+    }
+  }
+}
+
+#undef BSE_PROJ_S1
+
+// B_mu alone: one workgroup per orbit and block
+__global__ __launch_bounds__(256) void k_project_vec(int nb, ProjList P,
+                                                     const double2 *__restrict__ B) {
+  project_vec(P.b[blockIdx.y], blockIdx.x, nb, B);
 }
 
 // |B_mu|^2 = sum over the block's orbits and basis vectors of |sum_{k in O}
@@ -268,6 +387,30 @@ __global__ void k_dipole_select(int nblk, const double *__restrict__ w, double r
   *active = best;
 }
 
+constexpr int PROJ_MAXCOL = 2048;  // |S| nv nc, at most
+
+ProjBlk proj_blk(const bse_block &b, void *Hmu, int64_t ldmu, double2 *Bmu) {
+  return ProjBlk{b.mem_off, b.members, b.orb_off, b.orb_dim, b.ub_off, b.ubasis, Hmu, ldmu, Bmu};
+}
+
+// Bands per workgroup: as many as leave PWGS workgroups (the tables of a
+// workgroup are three dependent loads; 8^3 with 4 + 4 bands: 182 us, 196 with
+// 20000 and 213 with 4096 workgroups).
+constexpr int PWGS = 8192;
+template <typename T, bool SEEDSRC>
+int32_t launch_project(const char *name, const bse_problem *p, const void *H, int64_t ldh,
+                       const ProjList &L, const SeedSrc &sd, const double2 *B, hipStream_t s) {
+  const int nb = p->nv * p->nc;
+  const size_t lds = PMAXL * nb > PNT ? sizeof(double2) * PMAXR * PMAXR * nb : 0;
+  const int64_t wgs = int64_t(p->nkorb) * p->nkorb * nb * L.n;
+  const int bpw = int(std::max<int64_t>(1, std::min<int64_t>(nb, wgs / PWGS)));
+  const dim3 g((unsigned)((nb + bpw - 1) / bpw * L.n), (unsigned)p->nkorb, (unsigned)p->nkorb);
+  BSE_LAUNCH(name, (k_project<T, SEEDSRC>), g, dim3(PNT), lds, s, p->nv, p->nc, (const T *)H, ldh, L,
+             sd, B, bpw);
+  BSE_HIP_CHECK(hipGetLastError());
+  return BSE_OK;
+}
+
 }  // namespace
 }  // namespace bse
 
@@ -311,9 +454,8 @@ extern "C" int32_t bse_project_blocks(const bse_problem *p, const void *H, int64
   if (n1 < 1 || n2 < 1 || n3 < 1 || p->nv < 1 || p->nc < 1 || p->nkorb < 1)
     return fail(BSE_ESHAPE, "bad problem sizes");
   const int64_t nk = int64_t(n1) * n2 * n3, nb = int64_t(p->nv) * p->nc, N = nk * nb;
-  if (nb > 128 * PMAXCOL * 2) return fail(BSE_EUNSUPPORTED, "nv nc too large for projection");
+  if (int64_t(PMAXL) * nb > PROJ_MAXCOL) return fail(BSE_EUNSUPPORTED, "nv nc too large for projection");
   hipStream_t s = (hipStream_t)stream;
-  if (int64_t(PMAXL) * nb > PCH) return fail(BSE_EUNSUPPORTED, "nv nc too large for projection");
   for (int ib = 0; ib < nblk; ++ib) {
     const bse_block &b = blk[ib];
     if (b.n < 0 || !b.mem_off || !b.members || !b.orb_off || !b.orb_dim || !b.ub_off || !b.ubasis)
@@ -323,35 +465,44 @@ extern "C" int32_t bse_project_blocks(const bse_problem *p, const void *H, int64
       if (!H) return fail(BSE_EINVAL, "H is NULL");
       if (ldh < N) return fail(BSE_ESHAPE, "ldh < N");
       if (!ldmu || ldmu[ib] < b.n) return fail(BSE_ESHAPE, "ldmu[%d] < n", ib);
-      if (9 * nb > PNT * PMAXCOL)
-        return fail(BSE_EUNSUPPORTED, "r' nv nc exceeds %d columns", PNT * PMAXCOL);
-      dim3 g((unsigned)nb, (unsigned)p->nkorb, (unsigned)p->nkorb);
-      const bool one = 9 * nb <= PNT;  // every output column of a block row in one thread
-#define BSE_PROJ(T, NCT, PR)                                                                  \
-  BSE_LAUNCH("k_project", (k_project<T, false, NCT, PR>), g, dim3(PNT), 0, s, p->nv, p->nc,   \
-             (const T *)H, ldh, b.mem_off, b.members, b.orb_off, b.orb_dim, b.ub_off, b.ubasis, \
-             (T *)Hmu[ib], ldmu[ib], SeedSrc{})
-      // pairs of FP32 entries need nv nc even and 16-byte aligned rows
-      const bool pair = nb % 2 == 0 && ldh % 2 == 0 && (reinterpret_cast<uintptr_t>(H) & 15) == 0;
-      if (h_fp64) {
-        if (one) BSE_PROJ(double, 1, false); else BSE_PROJ(double, 2, false);
-      } else if (pair) {
-        if (one) BSE_PROJ(float, 1, true); else BSE_PROJ(float, 2, true);
-      } else {
-        if (one) BSE_PROJ(float, 1, false); else BSE_PROJ(float, 2, false);
-      }
-#undef BSE_PROJ
-      BSE_HIP_CHECK(hipGetLastError());
     }
-    if (Bmu && Bmu[ib]) {
-      if (!B) return fail(BSE_EINVAL, "B is NULL");
-      BSE_LAUNCH("k_project_vec", k_project_vec, dim3((unsigned)p->nkorb), dim3(256), 0, s, p->nkorb,
-                         (int)nb, b.mem_off, b.members, b.orb_off, b.orb_dim, b.ub_off, b.ubasis,
-                         (const double2 *)B, (double2 *)Bmu[ib]);
-      BSE_HIP_CHECK(hipGetLastError());
-    }
+    if (Bmu && Bmu[ib] && !B) return fail(BSE_EINVAL, "B is NULL");
   }
-  return BSE_OK;
+  const double2 *Bv = (const double2 *)B;
+  // blocks with H_mu wanted (their B_mu comes along), then B_mu alone
+  ProjList L{}, V{};
+  auto flush_h = [&]() -> int32_t {
+    if (L.n == 0) return BSE_OK;
+    const int32_t st =
+        h_fp64 ? launch_project<double, false>("k_project", p, H, ldh, L, SeedSrc{}, Bv, s)
+               : launch_project<float, false>("k_project", p, H, ldh, L, SeedSrc{}, Bv, s);
+    L.n = 0;
+    return st;
+  };
+  auto flush_v = [&]() -> int32_t {
+    if (V.n == 0) return BSE_OK;
+    BSE_LAUNCH("k_project_vec", k_project_vec, dim3((unsigned)p->nkorb, (unsigned)V.n), dim3(256),
+               0, s, (int)nb, V, Bv);
+    V.n = 0;
+    BSE_HIP_CHECK(hipGetLastError());
+    return BSE_OK;
+  };
+  for (int ib = 0; ib < nblk; ++ib) {
+    const bool h = Hmu && Hmu[ib], w = Bmu && Bmu[ib];
+    const ProjBlk e = proj_blk(blk[ib], h ? Hmu[ib] : nullptr, h ? ldmu[ib] : 0,
+                               w ? (double2 *)Bmu[ib] : nullptr);
+    int32_t st = BSE_OK;
+    if (h) {
+      L.b[L.n++] = e;
+      if (L.n == PMAXB) st = flush_h();
+    } else if (w) {
+      V.b[V.n++] = e;
+      if (V.n == PMAXB) st = flush_v();
+    }
+    if (st) return st;
+  }
+  const int32_t st = flush_h();
+  return st ? st : flush_v();
 }
 
 extern "C" int32_t bse_project_seed(int64_t plan, int32_t nblk, const bse_block *blk,
@@ -362,8 +513,7 @@ extern "C" int32_t bse_project_seed(int64_t plan, int32_t nblk, const bse_block 
   const bse_problem *p = &sp.p;
   if (nblk < 0 || (nblk > 0 && !blk)) return fail(BSE_EINVAL, "bad block list");
   const int64_t nb = int64_t(p->nv) * p->nc, N = int64_t(sp.nk) * nb;
-  if (int64_t(PMAXL) * nb > PCH || 9 * nb > PNT * PMAXCOL)
-    return fail(BSE_EUNSUPPORTED, "nv nc too large for projection");
+  if (int64_t(PMAXL) * nb > PROJ_MAXCOL) return fail(BSE_EUNSUPPORTED, "nv nc too large for projection");
   hipStream_t s = (hipStream_t)stream;
   const SeedSrc sd{p->korb, sp.porb, p->ev, p->ec, sp.xs, sp.drep, sp.ldx, sp.nk, 1.0 / sp.nk};
   for (int ib = 0; ib < nblk; ++ib) {
@@ -373,19 +523,17 @@ extern "C" int32_t bse_project_seed(int64_t plan, int32_t nblk, const bse_block 
       return fail(BSE_EINVAL, "block %d has NULL arrays", ib);
     if (b.n > N) return fail(BSE_ESHAPE, "block %d larger than N", ib);
     if (!ldmu || ldmu[ib] < b.n) return fail(BSE_ESHAPE, "ldmu[%d] < n", ib);
-    dim3 g((unsigned)nb, (unsigned)p->nkorb, (unsigned)p->nkorb);
-    const bool one = 9 * nb <= PNT;
-#define BSE_PROJS(T, NCT)                                                                     \
-  BSE_LAUNCH("k_project_seed", (k_project<T, true, NCT>), g, dim3(PNT), 0, s, p->nv, p->nc,   \
-             nullptr, 0, b.mem_off, b.members, b.orb_off, b.orb_dim, b.ub_off, b.ubasis,       \
-             (T *)Hmu[ib], ldmu[ib], sd)
-    if (sp.prec == BSE_FP64) {
-      if (one) BSE_PROJS(double, 1); else BSE_PROJS(double, 2);
-    } else {
-      if (one) BSE_PROJS(float, 1); else BSE_PROJS(float, 2);
-    }
-#undef BSE_PROJS
-    BSE_HIP_CHECK(hipGetLastError());
+  }
+  ProjList L{};
+  for (int ib = 0; ib <= nblk; ++ib) {
+    if (ib < nblk && Hmu && Hmu[ib]) L.b[L.n++] = proj_blk(blk[ib], Hmu[ib], ldmu[ib], nullptr);
+    if (L.n == 0 || (ib < nblk && L.n < PMAXB)) continue;
+    const int32_t rc =
+        sp.prec == BSE_FP64
+            ? launch_project<double, true>("k_project_seed", p, nullptr, 0, L, sd, nullptr, s)
+            : launch_project<float, true>("k_project_seed", p, nullptr, 0, L, sd, nullptr, s);
+    if (rc) return rc;
+    L.n = 0;
   }
   return BSE_OK;
 }
