@@ -23,7 +23,7 @@
 //               products with V and W come out of one pass.
 //     All scalar work is FP64; A is stored in FP64 or (prec FP32) FP32.
 //  3. T is real symmetric tridiagonal (the reflectors make the subdiagonal
-//     real).  All eigenvalues by 64-way multisection on Sturm counts (one wave
+//     real).  All eigenvalues by multisection on Sturm counts (a group of lanes
 //     per eigenvalue, FP64).  Because Q0 Q maps e_1 to e_1,
 //     |B_l|^2 = beta0^2 z_l(0)^2 with z_l the eigenvectors of T, and for a
 //     cluster of (numerically) degenerate eigenvalues the summed weight is the
@@ -1282,53 +1282,113 @@ __device__ __forceinline__ void b_tri_prep(int64_t n, const double *__restrict__
   }
 }
 
-// number of eigenvalues of T below x (LDL^T Sturm sequence with pivot guard).
-// d and e2 are the same for every lane.  Whole blocks of SU steps read their
-// inputs one block ahead (contiguous uniform loads), so the dependent chain of
-// the recurrence does not wait for a load at every step; the last partial
-// block loads as it goes.
+// Number of eigenvalues of T below x: the sign changes of the Sturm sequence
+// p_k = (d_k - x) p_{k-1} - e_{k-1}^2 p_{k-2}.  One FMA per step is on the dependent
+// chain, where the ratios q_k = p_k / p_{k-1} need a reciprocal (n = 2160: 270
+// cycles a step; the whole bisection 1.70 ms, now 0.65 ms, n = 10080: 21.5 ms,
+// now 4.7 ms).  The pair (p_k, p_{k-1}) is brought back to a magnitude of one
+// after every SU steps by a power of two, so the rounding is that of the
+// recurrence alone (a relative error of a few eps in d_k - x and e^2, as for the
+// ratios).  A block that leaves the range (an exact zero pivot at a split, tiny
+// or huge entries, NaN) is repeated with the ratios and their pivot guard.
+// d and e2 are the same for every lane: the workgroup stages them in LDS, SCH
+// steps at a time and the next SCH in flight, and a step reads its pair as one
+// broadcast.  (Read as scalars through the constant cache the steps waited for
+// the loads: 120 cycles each at n = 10080.)  Every thread of the workgroup takes
+// part in every call.
 constexpr int SU = 8;
-__device__ __forceinline__ int sturm_count(const double *__restrict__ d,
-                                           const double *__restrict__ e2, int64_t n, double x,
-                                           double pivmin) {
-  int cnt = 0;
-  double q = d[0] - x;
-  if (fabs(q) < pivmin) q = -pivmin;
-  cnt += q < 0;
-  auto step = [&](double dk, double ek) {
-    q = dk - x - ek * rcp64(q);
+constexpr int SCH = 512;  // steps staged at a time
+__device__ __forceinline__ unsigned sign_bit(double x) {
+  return static_cast<unsigned>(static_cast<unsigned long long>(__double_as_longlong(x)) >> 63);
+}
+__device__ __forceinline__ unsigned sign_change(double x, double y) {
+  return static_cast<unsigned>(
+      static_cast<unsigned long long>(__double_as_longlong(x) ^ __double_as_longlong(y)) >> 63);
+}
+struct SturmState {
+  double p, pp;
+  unsigned cnt;
+};
+// len <= SU steps, their pairs (d_k, e_{k-1}^2) in registers (r) and in LDS (m)
+__device__ __forceinline__ void sturm_block(SturmState &S, const double2 (&r)[SU], const double2 *m,
+                                            int len, double x, double pivmin) {
+  double p = S.p, pp = S.pp;
+  unsigned cnt = S.cnt;
+#pragma unroll
+  for (int u = 0; u < SU; ++u) {
+    if (u >= len) break;
+    const double pn = fma(r[u].x - x, p, -(r[u].y * pp));
+    cnt += sign_change(pn, p);
+    pp = p;
+    p = pn;
+  }
+  const double mx = fmax(fabs(p), fabs(pp));
+  if (mx > 1e-200 && mx < 1e200) {
+    const int ex = __builtin_amdgcn_frexp_exp(mx);
+    S = SturmState{__builtin_amdgcn_ldexp(p, -ex), __builtin_amdgcn_ldexp(pp, -ex), cnt};
+    return;
+  }
+  // repeat the block with q = p / pp and its guard
+  double q = S.pp != 0.0 ? S.p / S.pp : 1e200;  // (pp = 0: the next step drops e^2 / q)
+  cnt = S.cnt;
+  if (fabs(q) < pivmin) {
+    if (!sign_bit(q)) ++cnt;  // counted as positive; the guard makes it negative
+    q = -pivmin;
+  }
+#pragma unroll 1
+  for (int u = 0; u < len; ++u) {
+    q = m[u].x - x - m[u].y / q;
     if (fabs(q) < pivmin) q = -pivmin;
     cnt += q < 0;
-  };
-  int64_t k = 1;
-  if (k + SU <= n) {
-    double dn[SU], en[SU];
+  }
+  S = SturmState{q, 1.0, cnt};
+}
+__device__ __forceinline__ int sturm_count(const double *__restrict__ d,
+                                           const double *__restrict__ e2, int n, double x,
+                                           double pivmin, double2 (&sh)[2][SCH]) {
+  constexpr int PT = SCH / ENT;  // pairs staged per thread
+  const int nst = n - 1;         // steps; pair j is (d[j + 1], e2[j])
+  SturmState S;
+  S.p = d[0] - x;
+  S.pp = 1.0;
+  S.cnt = sign_bit(S.p);
+  double2 nx[PT];
+  auto fetch = [&](int j0) {
 #pragma unroll
-    for (int u = 0; u < SU; ++u) {
-      dn[u] = d[k + u];
-      en[u] = e2[k - 1 + u];
+    for (int u = 0; u < PT; ++u) {
+      const int j = std::min(j0 + int(threadIdx.x) + ENT * u, nst - 1);
+      nx[u] = double2{d[j + 1], e2[j]};
     }
-    for (; k + SU <= n; k += SU) {
-      double dc[SU], ec[SU];
+  };
+  if (nst > 0) fetch(0);
+  for (int j0 = 0, buf = 0; j0 < nst; j0 += SCH, buf ^= 1) {
+    // (the buffer written here was last read two chunks ago, before a barrier)
 #pragma unroll
-      for (int u = 0; u < SU; ++u) {
-        dc[u] = dn[u];
-        ec[u] = en[u];
-      }
-      if (k + 2 * SU <= n) {
-        const double *dp = d + k + SU, *ep = e2 + k + SU - 1;
+    for (int u = 0; u < PT; ++u) sh[buf][threadIdx.x + ENT * u] = nx[u];
+    __syncthreads();
+    if (j0 + SCH < nst) fetch(j0 + SCH);
+    const double2 *m = sh[buf];
+    const int len = std::min(SCH, nst - j0), full = len / SU * SU;
+    double2 ra[SU], rb[SU];
 #pragma unroll
-        for (int u = 0; u < SU; ++u) {
-          dn[u] = dp[u];
-          en[u] = ep[u];
-        }
-      }
+    for (int u = 0; u < SU; ++u) ra[u] = m[u];
+    for (int k = 0; k < full; k += 2 * SU) {  // (reads past len stay inside the buffer)
 #pragma unroll
-      for (int u = 0; u < SU; ++u) step(dc[u], ec[u]);
+      for (int u = 0; u < SU; ++u) rb[u] = m[std::min(k + SU, SCH - SU) + u];
+      sturm_block(S, ra, m + k, SU, x, pivmin);
+      if (k + SU >= full) break;
+#pragma unroll
+      for (int u = 0; u < SU; ++u) ra[u] = m[std::min(k + 2 * SU, SCH - SU) + u];
+      sturm_block(S, rb, m + k + SU, SU, x, pivmin);
+    }
+    if (full < len) {
+#pragma unroll
+      for (int u = 0; u < SU; ++u) ra[u] = m[std::min(full + u, len - 1)];
+      sturm_block(S, ra, m + full, len - full, x, pivmin);
     }
   }
-  for (; k < n; ++k) step(d[k], e2[k - 1]);
-  return cnt;
+  __syncthreads();  // the next call may write the buffer read last
+  return int(S.cnt);
 }
 
 // x_g, g = 0 .. NGRID - 1: the interior points of a uniform grid over the
@@ -1343,56 +1403,58 @@ __device__ __forceinline__ void b_bisect_grid(int64_t n, const double *__restric
                                               const double *__restrict__ e2,
                                               const double *__restrict__ sc,
                                               int *__restrict__ grid, int wg) {
+  __shared__ double2 sh[2][SCH];
   const int g = wg * ENT + int(threadIdx.x);
-  grid[g] = sturm_count(d, e2, n, grid_x(sc, g), sc[3]);
+  grid[g] = sturm_count(d, e2, int(n), grid_x(sc, g), sc[3], sh);
 }
 
-// One wave per eigenvalue index: each pass evaluates 64 Sturm counts at the
-// interior points of the current interval (lane l at a + (l+1)(b-a)/65) and
-// keeps the sub-interval holding eigenvalue i; ~9 passes reach FP64 resolution
-// from the Gershgorin interval.  With grid (the counts of b_bisect_grid) the
-// start is the grid cell holding eigenvalue i, found in two ballots over
-// 64-entry segments, which saves two passes.
+// A group of G = g_bisect_lanes(n) lanes per eigenvalue index: each pass evaluates
+// G Sturm counts at the interior points of the current interval (lane l at
+// a + (l + 1)(b - a) / (G + 1)) and keeps the sub-interval holding eigenvalue i.
+// With grid (the counts of b_bisect_grid) the start is the grid cell holding
+// eigenvalue i, found by a binary search.
 __device__ __forceinline__ void b_bisect(int64_t n, const double *__restrict__ d,
                                                 const double *__restrict__ e2,
                                                 const double *__restrict__ sc,
                                                 const int *__restrict__ grid,
                                                 double *__restrict__ omega,
                                                 int32_t *__restrict__ status, int wg) {
-  const int lane = threadIdx.x & 63;
-  const int64_t i = int64_t(wg) * (blockDim.x / 64) + (threadIdx.x >> 6);
-  if (i >= n) return;
+  __shared__ double2 sh[2][SCH];
+  const int G = g_bisect_lanes(n), lane = threadIdx.x & 63, sl = lane & (G - 1), base = lane & ~(G - 1);
+  const int64_t ix = int64_t(wg) * (ENT / G) + threadIdx.x / G, i = ix < n ? ix : n - 1;
   double a = sc[0], b = sc[1];
   const double pivmin = sc[3];
   if (grid) {
     // count(x) = eigenvalues below x; the first g with count(x_g) > i gives
     // x_{g-1} <= lambda_i < x_g
-    const unsigned long long m1 = __ballot(grid[64 * lane + 63] > i);
-    if (m1) {
-      const int seg = __builtin_ctzll(m1);
-      const unsigned long long m2 = __ballot(grid[64 * seg + lane] > i);
-      const int g = 64 * seg + __builtin_ctzll(m2);  // m2 != 0: the segment's last entry is > i
-      b = grid_x(sc, g);
-      if (g > 0) a = grid_x(sc, g - 1);
-    } else {
-      a = grid_x(sc, NGRID - 1);
+    int lo = 0, hi = NGRID;  // every entry before lo is <= i, those from hi on are > i
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (grid[mid] > i) hi = mid; else lo = mid + 1;
+    }
+    if (lo < NGRID) b = grid_x(sc, lo);
+    if (lo > 0) a = grid_x(sc, lo - 1);
+  }
+  const unsigned long long gm = (G == 64 ? 0ull : 1ull << G) - 1ull;
+  bool open = true;  // (the same for the lanes of a group)
+  for (int pass = 0; pass < 64; ++pass) {
+    if (b - a <= 2.3e-16 * fmax(fabs(a), fabs(b)) + pivmin) open = false;
+    if (!__syncthreads_or(open)) break;
+    const double x = a + (b - a) * double(sl + 1) / double(G + 1);
+    const int cnt = sturm_count(d, e2, int(n), x, pivmin, sh);
+    // first lane of the group whose point has more than i eigenvalues below it
+    const unsigned long long m = (__ballot(cnt > i) >> base) & gm;
+    const int f = m ? __builtin_ctzll(m) : G;
+    const double na = f == 0 ? a : a + (b - a) * double(f) / double(G + 1);
+    const double nb = f == G ? b : a + (b - a) * double(f + 1) / double(G + 1);
+    if (!(na > a || nb < b)) open = false;  // no progress at this resolution
+    if (open) {
+      a = na;
+      b = nb;
     }
   }
-  for (int pass = 0; pass < 24; ++pass) {
-    if (b - a <= 2.3e-16 * fmax(fabs(a), fabs(b)) + pivmin) break;
-    const double x = a + (b - a) * double(lane + 1) / 65.0;
-    const int cnt = sturm_count(d, e2, n, x, pivmin);
-    // first lane whose point has more than i eigenvalues below it
-    const unsigned long long m = __ballot(cnt > i);
-    const int f = m ? __builtin_ctzll(m) : 64;
-    const double na = f == 0 ? a : a + (b - a) * double(f) / 65.0;
-    const double nb = f == 64 ? b : a + (b - a) * double(f + 1) / 65.0;
-    if (!(na > a || nb < b)) break;  // no progress at this resolution
-    a = na;
-    b = nb;
-  }
   const double x = 0.5 * (a + b);
-  if (lane == 0) {
+  if (sl == 0 && ix < n) {
     omega[i] = x;
     if (!isfinite(x)) atomicAdd(status + 1, 1);  // no finite eigenvalue (non-finite T)
   }

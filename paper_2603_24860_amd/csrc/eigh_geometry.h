@@ -264,6 +264,14 @@ __host__ __device__ __forceinline__ int64_t g_sb_voff(int64_t n, int64_t p) {
   return p * (n - SBW) - SBW * (p * (p - 1) / 2);
 }
 
+// Lanes per eigenvalue of the bisection: G lanes gain log2(G + 1) bits a pass, so
+// fewer lanes cost fewer Sturm counts in all (64: 7 passes of 64; 8: 13 of 8)
+// in a longer chain.  As many as keep about one wave per SIMD (n = 10080: 391 ms
+// the solve with 8 lanes, 397 with 64; n = 2160: 33.21 ms with 16, 33.31 with 64).
+__host__ __device__ __forceinline__ int g_bisect_lanes(int64_t n) {
+  return n <= 1024 ? 64 : (n <= 2048 ? 32 : (n <= 4096 ? 16 : 8));
+}
+
 // relative cluster tolerance of the weights: 8 eps sqrt(n) of the storage type of A
 __host__ __device__ __forceinline__ double ctol_rel(int64_t n, bool a_fp64) {
   const double eps_w = a_fp64 ? 2.2e-16 : 1.2e-7;
@@ -376,7 +384,8 @@ int64_t kind_wgs(int kind, int64_t n, int64_t j, int wpr, int htile = 0) {
     }
     case K_TRI: return 1;
     case K_BGRID: return NGRID / ENT;
-    default: return cdiv(n, 4);  // bisect, weights
+    case K_BISECT: return cdiv(n, ENT / g_bisect_lanes(n));
+    default: return cdiv(n, 4);  // weights
   }
 }
 
