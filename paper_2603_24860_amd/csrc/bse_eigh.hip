@@ -1608,6 +1608,8 @@ static_assert(RB == RB_ROWS, "k_colB rows per workgroup");
   const Desc &D = Ds[lo_];                                                                \
   const int wg = int(blockIdx.x) - spre[lo_];
 
+#include "eigh_panel.h"
+
 #define BSE_PAIR(NAME, ARGS, ...)                                                         \
   template <typename TH, typename TA, int WPR>                                            \
   __global__ __launch_bounds__(ENT) void k_##NAME(Desc D, ARGS) {                         \
@@ -1646,6 +1648,7 @@ BSE_PAIR(rank2, int unused_, {
   const int64_t gx = g_rank2_gx(D.n);
   b_rank2<TA>(D.n, (TA *)D.A, D.lda, D.wraw, D.vbuf, D.part2, (int)g_nwg(D.n), D.tau, wg / gx,
               wg % gx, gx);
+  pan_clear(D, wg, D.n * gx, true);
 })
 BSE_PAIR(col0, int64_t j0 BSE_COMMA int cur, {
   b_col0<TA>(D.n, j0, (const TA *)D.A, D.lda, D.col, cur ? D.partb1 : D.partb0, wg);
@@ -1684,6 +1687,7 @@ __device__ __forceinline__ void her2k_wg(const Desc &D, int64_t j0, int wg) {
   constexpr int BN = HerTile<TA, S>::BN;
   const int nbk = g_nbk(D.n, j0);
   const int64_t c0 = j0 + nbk, t = cdiv(D.n - c0, BN);
+  pan_clear(D, wg, her_tri(t, BN) ? t * (t + 1) / 2 : t * t, false);
   if (!her_tri(t, BN)) {
     b_her2k<TA, S>(D.n, c0, nbk, D.V, D.W, D.ldv, (TA *)D.A, D.lda, wg % t, wg / t, false);
   } else {
@@ -2543,8 +2547,17 @@ int32_t eigh_run(int64_t n, const void *Hmu, int64_t ld, const void *Bmu, double
     }
     const int nbk = g_nbk(n, j0);
     if (K > 0) D.V = D0.Vall + j0 * D0.ldv;  // keep every reflector for the back-transform
-    BSE_LAUNCH("k_col0", (k_col0<TH, TA, 4>), grid(K_COL0, j0, 4), dim3(ENT), 0, s, D, j0, cur);
-    for (int i = 0; i < nbk; ++i) {
+    const bool pan = g_pan(n, j0, sizeof(TA) == 8);
+    if constexpr (sizeof(TA) == 8) if (pan) {
+      const size_t lds = size_t(n - j0) * sizeof(double2);
+      const dim3 g((unsigned)g_pan_wgs(n - j0 - 1));
+      if (g_pan_wr(n - j0 - 1) == 2)
+        BSE_LAUNCH("k_panel", (k_panel<2>), g, dim3(ENT), lds, s, D, j0);
+      else
+        BSE_LAUNCH("k_panel", (k_panel<3>), g, dim3(ENT), lds, s, D, j0);
+    }
+    if (!pan) BSE_LAUNCH("k_col0", (k_col0<TH, TA, 4>), grid(K_COL0, j0, 4), dim3(ENT), 0, s, D, j0, cur);
+    for (int i = 0; !pan && i < nbk; ++i) {
       const int64_t jn = j0 + i, m = n - jn - 1;
       const int wpr = single_wpr(m);
 #define BSE_COLA(W)                                                                         \
@@ -2700,6 +2713,10 @@ inline bool takes_two_stage(int64_t n, int64_t) { return n >= g_two_stage_min.lo
 // ---------------------------------------------------------------------------
 // batched: every active block advances one step per launch
 // ---------------------------------------------------------------------------
+// workgroups of one batched k_panel launch, at most (a third of a compute unit
+// each: one batch and one single panel fit on the device side by side)
+constexpr int PAN_BATCH = 512;
+
 struct BatchLaunch {
   int kind;
   int64_t j;
@@ -2707,6 +2724,8 @@ struct BatchLaunch {
   int nact;
   int total;
   size_t pre_off;  // ints into the prefix table
+  int b0;          // first block (k_panel)
+  size_t lds;      // dynamic LDS (k_panel)
 };
 
 struct BatchPlan {
@@ -2725,11 +2744,14 @@ void plan_launches(BatchPlan &P, std::vector<int> &pre) {
   pre.clear();
   const int nb = P.nb;
   auto add = [&](int kind, int64_t j, int cur) {
-    BatchLaunch L{kind, j, cur, 0, 0, pre.size()};
+    BatchLaunch L{kind, j, cur, 0, 0, pre.size(), 0, 0};
     int64_t tot = 0;
     pre.push_back(0);
     for (int b = 0; b < nb; ++b) {
-      const int64_t w = kind_wgs<TA>(kind, P.n[b], j, P.wpr, P.htile);
+      // (the largest blocks' panels may still run column by column)
+      const bool col = kind == K_COL0 || kind == K_COLA || kind == K_COLB;
+      const int64_t w = col && g_pan(P.n[b], j - j % NBK, sizeof(TA) == 8)
+                            ? 0 : kind_wgs<TA>(kind, P.n[b], j, P.wpr, P.htile);
       if (w == 0) break;  // sorted descending: the rest are inactive too
       tot += w;
       pre.push_back((int)tot);
@@ -2749,6 +2771,26 @@ void plan_launches(BatchPlan &P, std::vector<int> &pre) {
   add(K_W0, 0, 0);
   add(K_RANK2, 0, 0);
   int cur = 0;
+  // panels of one launch each: as many blocks per launch as PAN_BATCH workgroups
+  // hold, all of one row count per workgroup
+  auto panels = [&](int64_t j0) {
+    auto on = [&](int b) { return b < nb && g_pan(P.n[b], j0, sizeof(TA) == 8); };
+    int b = 0;
+    while (b < nb && j0 < g_tail0(P.n[b]) && !on(b)) ++b;
+    while (on(b)) {
+      BatchLaunch L{K_PANEL, j0, g_pan_wr(P.n[b] - j0 - 1), 0, 0, pre.size(), b,
+                    size_t(P.n[b] - j0) * sizeof(double2)};
+      pre.push_back(0);
+      for (; on(b) && g_pan_wr(P.n[b] - j0 - 1) == L.cur; ++b) {
+        const int w = g_pan_wgs(P.n[b] - j0 - 1);
+        if (L.nact > 0 && L.total + w > PAN_BATCH) break;
+        L.total += w;
+        pre.push_back(L.total);
+        ++L.nact;
+      }
+      P.launches.push_back(L);
+    }
+  };
   for (int64_t j0 = 0; j0 < nmax; j0 += NBK) {
     add(K_COL0, j0, cur);
     for (int i = 0; i < NBK && j0 + i < nmax; ++i) {
@@ -2757,11 +2799,12 @@ void plan_launches(BatchPlan &P, std::vector<int> &pre) {
       add(K_COLB, jn, cur);
       cur ^= 1;
     }
+    panels(j0);
     add(K_HER2K, j0, cur);
   }
   // every block's tail in one launch: a block's working copy is not touched
   // after its last panel, so the tails need not sit in the lockstep chain
-  P.launches.push_back(BatchLaunch{K_TAIL, 0, 0, nb, nb, 0});
+  P.launches.push_back(BatchLaunch{K_TAIL, 0, 0, nb, nb, 0, 0, 0});
   add(K_TRI, 0, 0);
   add(K_BGRID, 0, 0);
   add(K_BISECT, 0, 0);
@@ -2787,6 +2830,14 @@ int32_t batch_launch(const BatchPlan &P, const BatchLaunch &L, hipStream_t s) {
         BSE_LAUNCH("k_her2k", (k_her2k_b<TH, TA, 1>), g, b, 0, s, Ds, pre, L.nact, L.j);
       else
         BSE_LAUNCH("k_her2k", (k_her2k_b<TH, TA, 0>), g, b, 0, s, Ds, pre, L.nact, L.j);
+      break;
+    case K_PANEL:
+      if constexpr (sizeof(TA) == 8) {
+        if (L.cur == 2)
+          BSE_LAUNCH("k_panel", (k_panel_b<2>), g, b, L.lds, s, Ds + L.b0, pre, L.nact, L.j);
+        else
+          BSE_LAUNCH("k_panel", (k_panel_b<3>), g, b, L.lds, s, Ds + L.b0, pre, L.nact, L.j);
+      }
       break;
     case K_TRI: BSE_LAUNCH("k_tri_prep", k_tri_prep_b<TA>, g, dim3(RNT), 0, s, Ds, pre, L.nact, 0); break;
     case K_TAIL: BSE_LAUNCH("k_tail", k_tail_b<TA>, g, dim3(TNT), 0, s, Ds, L.cur, L.j); break;
@@ -2831,7 +2882,8 @@ size_t batch_ws_bytes(int32_t nb, const int64_t *h_n, bool a_fp64, std::vector<s
 size_t pre_bound(int32_t nb, const int64_t *h_n) {
   int64_t nmax = 0;
   for (int b = 0; b < nb; ++b) nmax = std::max(nmax, h_n[b]);
-  const size_t launches = 9 + size_t(cdiv(nmax, NBK)) * (2 * NBK + 2);  // 9 one-off kinds
+  // 9 one-off kinds; the k_panel launches of one panel index hold at most 2 nb entries
+  const size_t launches = 9 + size_t(cdiv(nmax, NBK)) * (2 * NBK + 2 + 2);
   return launches * size_t(nb + 1);
 }
 
@@ -2890,7 +2942,9 @@ extern "C" int32_t bse_block_eigh(int64_t n, const void *Hmu, int64_t ld, int32_
 // device address comes from hipGetSymbolAddress, once per device, with that
 // device current, and only that address is passed to kernels.
 constexpr size_t SCRATCH_BYTES = size_t(128) << 20;
-static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
+// the exchange words of k_panel come on top (at most PAN_WGS workgroups' worth)
+constexpr size_t SCRATCH_PAN = size_t(2) << 20;
+static __device__ __align__(256) unsigned char scratch[SCRATCH_BYTES + SCRATCH_PAN];
 
 namespace {
 constexpr int SCRATCH_MAX_DEV = 64;
@@ -2934,8 +2988,9 @@ extern "C" int32_t bse_block_eigh_noalloc(int64_t n, const void *Hmu, int64_t ld
   if (nrefine < 0 || nrefine > KMAX)
     return fail(BSE_EINVAL, "nrefine = %d outside 0 .. %d", nrefine, KMAX);
   const int64_t K = std::min<int64_t>(nrefine, n);
-  const size_t need = ws_layout(n, prec == BSE_FP64, nullptr, nullptr, K);
-  if (need > SCRATCH_BYTES)
+  const bool a64 = prec == BSE_FP64;
+  const size_t pan = g_pan_bytes(n, a64), need = ws_layout(n, prec == BSE_FP64, nullptr, nullptr, K) - pan;
+  if (need > SCRATCH_BYTES || pan > SCRATCH_PAN)
     return fail(BSE_EWORKSPACE,
                 "n = %lld needs %zu bytes of workspace; the static scratch holds %zu",
                 (long long)n, need, SCRATCH_BYTES);

@@ -92,6 +92,7 @@ struct Desc {
   double *scr;               // [K][6 CMAX n] inverse-iteration scratch
   double *wref;              // [K] refined eigenvalues
   double2 *Tm;               // [cdiv(n - 1, NBK)][NBK][NBK] block-reflector factors T
+  unsigned long long *px;    // exchange words of k_panel: entry counters, then four ring slots
   int32_t *clo;              // [n] first index of each eigenvalue's cluster in the weights
   // two-stage reduction (full -> band of width SBW -> tridiagonal); null
   // unless the block takes that path
@@ -206,6 +207,40 @@ __host__ __device__ __forceinline__ int64_t g_yslots(int64_t n) {
   return std::max<int64_t>(s, cdiv(n + 63, 256));
 }
 
+// FP64 storage: panels whose trailing block has at most PAN_M rows run as one
+// launch (k_panel).  FP32 storage keeps a launch per half column: past the
+// exhaustion of the Krylov space of a degenerate block the reduction's directions
+// are those of its rounding, the FP32 rounding of the working copy follows them,
+// and another order of the sums moves the strengths by 5e-6 (energies 1e-8 of the
+// norm, as far from the exact ones as before: 1.1e-8 and 1.2e-8 at n = 2160).  They
+// are kept as they are, at 33 ms where the panels took 24 (n = 2160).
+// k_panel:
+// g_pan_rows(m) rows per workgroup, a multiple of its four waves, so that at most
+// PAN_WGS workgroups share a panel.
+constexpr int PAN_WGS = 192;
+constexpr int64_t PAN_M = 12 * PAN_WGS;
+__host__ __device__ __forceinline__ int g_pan_wr(int64_t m) { return m <= 8 * PAN_WGS ? 2 : 3; }
+__host__ __device__ __forceinline__ int g_pan_rows(int64_t m) { return 4 * g_pan_wr(m); }
+__host__ __device__ __forceinline__ int g_pan_wgs(int64_t m) {
+  return (int)cdiv(m, g_pan_rows(m));
+}
+__host__ __device__ __forceinline__ bool g_pan(int64_t n, int64_t j0, bool a_fp64) {
+  return a_fp64 && j0 < g_tail0(n) && n - j0 - 1 <= PAN_M;
+}
+__host__ __device__ __forceinline__ int64_t g_pan_gmax(int64_t n) {
+  return n <= 8 * PAN_WGS ? cdiv(n, 8) : PAN_WGS;
+}
+// words: two entry counters per panel, then per ring slot the column (n), the
+// records (2 NBK per workgroup), the sums of y^dag v, the panel dot products, the
+// head row and y[m0], all complex
+__host__ __device__ __forceinline__ int64_t g_pan_ctrl(int64_t n) { return cdiv(n, NBK); }
+__host__ __device__ __forceinline__ int64_t g_pan_ring(int64_t n) {
+  return 2 * (n + (2 * NBK + 1) * g_pan_gmax(n) + 4 * NBK + 1);
+}
+__host__ __device__ __forceinline__ int64_t g_pan_words(int64_t n) {
+  return 2 * g_pan_ctrl(n) + 4 * g_pan_ring(n);
+}
+
 // two-stage geometry: workgroups of the panel kernels over m panel rows
 __host__ __device__ __forceinline__ int64_t g_sb_nw(int64_t m) { return m < 1 ? 1 : cdiv(m, SBR); }
 // complex K of one split of the panel product (a multiple of the FP32 slab, 32)
@@ -279,6 +314,11 @@ __host__ __device__ __forceinline__ double ctol_rel(int64_t n, bool a_fp64) {
 }
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
+
+// bytes of the exchange words (the last region of a one-stage layout)
+inline size_t g_pan_bytes(int64_t n, bool a_fp64) {
+  return a_fp64 && g_tail0(n) > 0 ? align256(size_t(g_pan_words(n)) * 8) : 0;
+}
 
 // Lays out one block's workspace at base (nullptr: size only).
 inline size_t ws_layout(int64_t n, bool a_fp64, Desc *w, char *base, int64_t K = 0,
@@ -354,13 +394,14 @@ inline size_t ws_layout(int64_t n, bool a_fp64, Desc *w, char *base, int64_t K =
       t.bxw = (double2 *)take(size_t(cdiv(n, BPR)) * K * SBW * 16);
     }
   }
+  if (!two_stage) t.px = g_pan_bytes(n, a_fp64) ? (unsigned long long *)take(g_pan_bytes(n, a_fp64)) : nullptr;
   if (w) *w = t;
   return off;
 }
 
 // workgroups of one launch kind for one block (0 = the block is not active)
 enum Kind { K_COPY, K_LOADB, K_HEMV0, K_W0, K_RANK2, K_COL0, K_COLA, K_COLB, K_HER2K, K_TRI,
-            K_BISECT, K_WEIGHTS, K_TAIL, K_BGRID };
+            K_BISECT, K_WEIGHTS, K_TAIL, K_BGRID, K_PANEL };
 
 template <typename TA>
 int64_t kind_wgs(int kind, int64_t n, int64_t j, int wpr, int htile = 0) {
@@ -383,6 +424,7 @@ int64_t kind_wgs(int kind, int64_t n, int64_t j, int wpr, int htile = 0) {
       return m > 0 ? (her_tri(t, bn) ? t * (t + 1) / 2 : t * t) : 0;
     }
     case K_TRI: return 1;
+    case K_PANEL: return g_pan(n, j, sizeof(TA) == 8) ? g_pan_wgs(n - j - 1) : 0;
     case K_BGRID: return NGRID / ENT;
     case K_BISECT: return cdiv(n, ENT / g_bisect_lanes(n));
     default: return cdiv(n, 4);  // weights
