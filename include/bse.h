@@ -317,8 +317,8 @@ int32_t bse_block_eigh(int64_t n, const void *Hmu, int64_t ld, int32_t h_fp64, c
  * per column, then the two-sided update A22 - V W^dag - W V^dag of the
  * trailing block with X = A22 V T formed on the matrix cores), then from the
  * band to the real tridiagonal by chasing each column's bulge down the band
- * (one task of one wave per step; launch t runs every step k of sweep i with
- * 2 i + k = t).  The tridiagonal step is the one above.  FP32 storage keeps
+ * (one launch: a workgroup takes a sweep and follows the sweep before it two
+ * steps behind).  The tridiagonal step is the one above.  FP32 storage keeps
  * the working copy in FP32 (its products summed in FP64 every 128 terms);
  * the panel, the band and the chase are FP64.  The workspace grows by about
  * 6.5 KB per row of the block (66 MB at n = 10080).  With nrefine > 0 the

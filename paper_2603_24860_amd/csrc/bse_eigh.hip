@@ -1228,15 +1228,6 @@ __device__ __forceinline__ void b_her2k(int64_t n, int64_t c0, int nbk,
 // ---------------------------------------------------------------------------
 // tridiagonal eigenvalues (multisection) and cluster weights
 // ---------------------------------------------------------------------------
-// 1 / x to full double precision: hardware estimate plus two Newton steps
-// (arguments are kept away from zero and denormals by the pivot guard).
-__device__ __forceinline__ double rcp64(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(r, fma(-x, r, 1.0), r);
-  r = fma(r, fma(-x, r, 1.0), r);
-  return r;
-}
-
 // scalars: [0] Gershgorin low, [1] high, [2] |T| (max row sum), [3] pivmin,
 // [4] cluster gap tolerance
 __device__ __forceinline__ void b_tri_prep(int64_t n, const double *__restrict__ d,
@@ -2663,16 +2654,13 @@ int32_t eigh_run_2s(int64_t n, const void *Hmu, int64_t ld, const void *Bmu, dou
     BSE_HIP_CHECK(hipGetLastError());
   }
   BSE_LAUNCH("k_sb_bandtail", k_sb_bandtail<TA>, dim3(1), dim3(ENT), 0, s, D, j0);
-  // ---- stage 2: band -> tridiagonal, launch t runs the tasks 2 i + k = t ----
-  for (int64_t t = 0; t <= g_bc_tmax(n); ++t) {
-    const int64_t lo = g_bc_ilo(n, t), hi = g_bc_ihi(n, t);
-    if (lo > hi) continue;
+  // ---- stage 2: band -> tridiagonal ----
+  if (n >= 2) {
+    const dim3 g((unsigned)std::min<int64_t>(n - 1, CHASE_WGS));
     if (K > 0)
-      BSE_LAUNCH("k_sb_chase", k_sb_chase<true>, dim3((unsigned)(hi - lo + 1)), dim3(BCT), 0, s,
-                 D, t, hi);
+      BSE_LAUNCH("k_sb_chase", k_sb_chase<true>, g, dim3(BCT), 0, s, D);
     else
-      BSE_LAUNCH("k_sb_chase", k_sb_chase<false>, dim3((unsigned)(hi - lo + 1)), dim3(BCT), 0, s,
-                 D, t, hi);
+      BSE_LAUNCH("k_sb_chase", k_sb_chase<false>, g, dim3(BCT), 0, s, D);
   }
   BSE_LAUNCH("k_sb_diag", k_sb_diag, dim3((unsigned)cdiv(n, ENT)), dim3(ENT), 0, s, D);
   BSE_HIP_CHECK(hipGetLastError());

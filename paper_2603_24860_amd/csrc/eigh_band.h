@@ -24,8 +24,8 @@
 // diagonal block of those rows; the right-hand application to the block
 // below creates a bulge whose first column the next step annihilates, and so
 // on down the band (the rest of each bulge is removed by later sweeps).  Step
-// k of sweep i runs after step k + 1 of sweep i - 1, so launch t runs every
-// step with 2 i + k = t.  The band with the fill of one bulge is stored
+// k of sweep i runs after step k + 1 of sweep i - 1, so a sweep follows the one
+// before it two steps behind, all of them in one launch.  The band with the fill of one bulge is stored
 // column by column, band[c][r - c] for 0 <= r - c < 2 SBW.
 
 // Component-wise select of complex values: a conditional on whole double2
@@ -301,6 +301,12 @@ __device__ __forceinline__ void b_sb_tmat(const Desc &D, int64_t j0, int nw) {
   }
 }
 
+// finished tasks of sweep i, and the next sweep to take (zeroed by k_sb_bandtail)
+__device__ __forceinline__ int *chase_done(const Desc &D, int64_t i) {
+  return reinterpret_cast<int *>(D.rfl + i * SBW);
+}
+__device__ __forceinline__ int *chase_next(const Desc &D) { return reinterpret_cast<int *>(D.rtau); }
+
 // band columns j0 .. n - 1 of the last diagonal block (no panel below it)
 template <typename TA>
 __device__ __forceinline__ void b_sb_bandtail(const Desc &D, int64_t j0) {
@@ -311,6 +317,8 @@ __device__ __forceinline__ void b_sb_bandtail(const Desc &D, int64_t j0) {
     const int64_t j = j0 + e / LDB, d = e % LDB, row = j + d;
     D.band[j * LDB + d] = (d <= SBW && row < n) ? to_d2(A[row * D.lda + j]) : double2{0, 0};
   }
+  for (int64_t i = threadIdx.x; i < n; i += ENT) *chase_done(D, i) = 0;  // of the chase
+  if (threadIdx.x == 0) *chase_next(D) = 0;
 }
 
 // V (column major, global rows) and U = V T in the storage type of A.  A
@@ -698,9 +706,98 @@ __global__ __launch_bounds__(ENT) void k_sb_her2k(Desc D, int64_t p0) {
   b_sb_her2k<TA>(D, p0, int(blockIdx.x));
 }
 
+// cross-lane moves within groups of eight lanes (DPP, no LDS round trip):
+// quad_perm [1,0,3,2] (lane ^ 1), [2,3,0,1] (lane ^ 2), [0,0,0,0] (lane 0 of
+// the quad) and row_half_mirror (lane i <-> 7 - i of each eight)
+constexpr int DPP_X1 = 0xB1, DPP_X2 = 0x4E, DPP_Q0 = 0x00, DPP_HM = 0x141;
+template <int CTRL>
+__device__ __forceinline__ double dppd(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp(int(b), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_mov_dpp(int(b >> 32), CTRL, 0xF, 0xF, false);
+  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo));
+}
+// sum over the eight lanes of a group, on every lane: the quad sums by two
+// exchanges, then the mirrored quad's sum
+__device__ __forceinline__ double sum8(double v) {
+  v += dppd<DPP_X1>(v);
+  v += dppd<DPP_X2>(v);
+  return v + dppd<DPP_HM>(v);
+}
+// the sum that exchanges with lanes ^ 16, ^ 8, .. ^ 1 give (bit for bit): after the
+// first a row of 16 has the period of the next, so row_ror:8, 4, 2, 1 stand for them
+__device__ __forceinline__ double bfly32(double v) {
+  v += __shfl_xor(v, 16, 64);
+  v += dppd<0x128>(v);
+  v += dppd<0x124>(v);
+  v += dppd<0x122>(v);
+  return v + dppd<0x121>(v);
+}
+// sums over 16, 32 and 64 lanes, on every lane: DPP moves within a row of 16
+// (row_mirror: lane i <-> 15 - i), LDS permutes only across rows
+__device__ __forceinline__ double sum16(double v) {
+  v = sum8(v);
+  return v + dppd<0x140>(v);
+}
+__device__ __forceinline__ double sum32(double v) {
+  v = sum16(v);
+  return v + __shfl_xor(v, 16, 64);
+}
+__device__ __forceinline__ double sum64(double v) {
+  v = sum32(v);
+  return v + __shfl_xor(v, 32, 64);
+}
+
+// 1 / x to full double precision: hardware estimate plus two Newton steps
+// (arguments are kept away from zero and denormals by the pivot guard).
+__device__ __forceinline__ double rcp64(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(r, fma(-x, r, 1.0), r);
+  r = fma(r, fma(-x, r, 1.0), r);
+  return r;
+}
+
+// `householder` with one reciprocal for the two quotients of each divisor: a / b as
+// q = a r, q + (a - b q) r with r = rcp64(b), the steps of a division in the normal
+// range.  It sits on the chain of every column and task.  Near the ends of the
+// range it is `householder` itself.
+__device__ __forceinline__ void fast_householder(double2 al, double xn2, double &beta, double2 &tau,
+                                                 double2 &scale) {
+  tau = scale = double2{0, 0};
+  beta = al.x;
+  if (xn2 == 0.0 && al.y == 0.0) return;
+  const double s = al.x * al.x + al.y * al.y + xn2;
+  if (!(s > 1e-290 && s < 1e290)) return householder(al, xn2, beta, tau, scale);
+  auto quot = [](double a, double b, double r) {
+    const double q = a * r;
+    return fma(fma(-b, q, a), r, q);
+  };
+  const double nrm = sqrt(s);
+  beta = al.x >= 0 ? -nrm : nrm;
+  const double rb = rcp64(beta);
+  tau = double2{quot(beta - al.x, beta, rb), quot(-al.y, beta, rb)};
+  const double2 den = {al.x - beta, al.y};
+  const double dd = den.x * den.x + den.y * den.y, rd = rcp64(dd);
+  scale = double2{quot(den.x, dd, rd), quot(-den.y, dd, rd)};
+}
+
 // ---------------------------------------------------------------------------
-// stage 2: bulge chasing, one task per workgroup
+// stage 2: bulge chasing, one sweep per workgroup at a time
 // ---------------------------------------------------------------------------
+// A workgroup takes the next sweep from a counter and runs its tasks down the
+// band; task (i, k) waits until sweep i - 1 has finished its task k + 1.  The sweep
+// it waits for was taken before its own by a workgroup that is running, and sweep
+// 0 waits for nobody, so every wait ends whatever number of workgroups the device
+// holds at a time.  The band goes from one sweep to the next through memory:
+// its words are read and written at agent scope, and a task's count goes out
+// after its words are complete: while the next task's blocks are on their way,
+// or at once when that task has to wait.  The reflector of a sweep stays in its
+// workgroup.  A serial chain bounds it: 2 n steps, each a task and the hop of its
+// words to the next workgroup.  One launch per step t = 2 i + k, every task of a
+// step its own workgroup, took 6.8 us a step (2.7 us of it the launch boundary):
+// n = 10080 137 ms; one launch with six barriers of 512 threads a task 114 ms;
+// now 104 ms, 5.1 us a step.
+//
 // Task (i, k) covers rows R_k = i + 1 + k SBW .. + L - 1:
 //   k > 0: the block O = A[R_k, R_{k-1}] takes the previous reflector of the
 //          sweep from the right; a new reflector annihilates its first column
@@ -709,171 +806,230 @@ __global__ __launch_bounds__(ENT) void k_sb_her2k(Desc D, int64_t p0) {
 //          beta);
 //   both: the two-sided update of the diagonal block D = A[R_k, R_k].
 // Thread t holds entries (p, q) = (t % 32, g + BCG u), g = t / 32, u < BCU,
-// of each block: a wave holds g = 2 w, 2 w + 1, so sums over q combine the
-// two halves of a wave and then the waves in LDS; sums over p are taken
-// from an LDS copy.  Loads are coalesced along p (the band is stored by
-// columns); D's upper triangle comes from its lower one through LDS.
-constexpr int BCT = 512;
+// of each block: a half-wave holds all p of its q, so sums over p stay in a wave;
+// sums over q combine the waves through LDS.  Loads are coalesced along p (the band
+// is stored by columns); D's upper triangle comes from its lower one through LDS.
+// Four barriers per task.  The order of every sum is part of the results: the
+// weights of eigenvalues 1e-8 apart (FP32 storage of a degenerate block) answer
+// to the last bit of the band by more than 1e-9.  So sums over q are those of
+// 16 groups q, q + 16, two groups to a part, parts in order; sums over p for the O
+// update those of row pairs, in order; products whose rounding the compiler
+// would choose otherwise from one form of this kernel to the next are written as fma
+// (with KEEP and without, as each form has rounded them from the first).
+constexpr int BCT = 256;
 constexpr int BCU = SBW * SBW / BCT;  // entries per thread and block
 constexpr int BCG = BCT / SBW;        // row groups g (q = g + BCG u)
-constexpr int BCR = SBW / BCG;        // rows p per group in the sums over p
 // KEEP (refinement): every reflector is also stored for the back-transformation
+constexpr int CHASE_WGS = 256;       // workgroups of the chase, at most
+constexpr int CHASE_SPIN = 1 << 26;  // polls of one wait (a minute; never reached)
+__device__ __forceinline__ double2 band_ld(const double2 *p) {
+  const double *q = reinterpret_cast<const double *>(p);
+  return double2{__hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                 __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)};
+}
+__device__ __forceinline__ void band_st(double2 *p, double2 v) {
+  double *q = reinterpret_cast<double *>(p);
+  __hip_atomic_store(q, v.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(q + 1, v.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 template <bool KEEP>
-__global__ __launch_bounds__(BCT) void k_sb_chase(Desc D, int64_t t, int64_t ihi) {
-  __shared__ double2 Ms[SBW][SBW + 1];      // D in full, then O
-  __shared__ double2 part[BCT / 64][SBW];   // per-wave sums over q
-  __shared__ double2 c0s[SBW];              // column 0 of O after the right update
-  __shared__ double2 zp[BCG][SBW];    // partial sums over p of conj(u) O
+__global__ __launch_bounds__(BCT) void k_sb_chase(Desc D) {
+  constexpr int NW = BCT / 64, NP = 8;
+  static_assert(BCU == 4 && BCG == 8 && NP == 2 * NW, "k_sb_chase: two parts per wave");
+  __shared__ double2 Ms[SBW][SBW + 1];  // D in full
+  __shared__ double2 part[NP][SBW];     // sums over four q each
+  __shared__ double zp[NW][16][2 * BCU + 1][2];  // per wave: sums of row pairs, [16][(u, half)][re, im]
+  __shared__ double2 zq[NW][2 * BCU];   // their sums
+  __shared__ double2 c0s[SBW];          // column 0 of O after the right update
+  __shared__ double2 us[SBW];           // the reflector of the previous task
   __shared__ double xsum;
-  const int64_t n = D.n, i = ihi - int64_t(blockIdx.x), k = t - 2 * i;
-  const int64_t rk = i + 1 + k * SBW, rp = k > 0 ? rk - SBW : i;
-  const int L = (int)std::min<int64_t>(SBW, n - rk);
+  __shared__ int sweep_s, done_s;
+  const int n = (int)D.n;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, p = tid % SBW, g = tid / SBW;
   double2 *band = D.band;
-  // ---- loads, all issued together from in-bounds addresses ----
-  double2 o[BCU], uq[BCU], dl[BCU];
-#pragma unroll
-  for (int u = 0; u < BCU; ++u) {
-    const int q = g + BCG * u;
-    const int64_t ao = k > 0 ? (rp + q) * LDB + SBW + p - q : i * LDB + 1 + p;
-    o[u] = band[ao];
-    uq[u] = D.rfl[i * SBW + q];
-    // lower triangle of D (q <= p), column by column
-    dl[u] = band[std::min<int64_t>(rk + q, n - 1) * LDB + (p >= q ? p - q : 0)];
-  }
-  const double2 tprev = D.rtau[i];
-#pragma unroll
-  for (int u = 0; u < BCU; ++u) {
-    const int q = g + BCG * u;
-    o[u] = csel(p < L && (k > 0 || q == 0), o[u], double2{0, 0});
-    const bool in = p < L && q <= p;
-    dl[u] = csel(in, dl[u], double2{0, 0});
-    if (q == p) dl[u].y = 0;
-    if (q <= p) {  // the entry and its mirror; upper positions are the mirrors' owners'
-      Ms[p][q] = dl[u];
-      Ms[q][p] = cconj(dl[u]);
-    }
-  }
-  // ---- k > 0: O <- O (I - tau u u^dag) ----
-  if (k > 0) {
-    double2 y = {0, 0};
-#pragma unroll
-    for (int u = 0; u < BCU; ++u) y = cadd(y, cmul(o[u], uq[u]));
-    y.x += __shfl_xor(y.x, 32, 64);
-    y.y += __shfl_xor(y.y, 32, 64);
-    if (lane < SBW) part[wv][p] = y;
-  }
-  __syncthreads();  // Ms (D in full) and the partial sums of O u
-  double2 dm[BCU];
-#pragma unroll
-  for (int u = 0; u < BCU; ++u) dm[u] = Ms[p][g + BCG * u];
-  if (k > 0) {
-    double2 y = part[0][p];
-#pragma unroll
-    for (int w = 1; w < BCT / 64; ++w) y = cadd(y, part[w][p]);
-    const double2 ty = cmul(tprev, y);
-#pragma unroll
-    for (int u = 0; u < BCU; ++u) o[u] = csub(o[u], cmul(ty, cconj(uq[u])));
-  }
-  // ---- new reflector from column 0 (held by the threads with g = 0, u = 0) ----
-  if (g == 0) c0s[p] = o[0];
-  if (wv == 0) {
-    // all 64 lanes take part in the sum (lanes 32 .. 63, g = 1, hold no
-    // column-0 entries and add 0)
-    double xs = (g == 0 && p >= 1 && p < L) ? o[0].x * o[0].x + o[0].y * o[0].y : 0.0;
-    xs = wave_sum(xs);
-    if (tid == 0) xsum = xs;
-  }
-  __syncthreads();  // c0s, xsum; the reads of Ms and part are done
-  double beta;
-  double2 tau, sc;
-  householder(c0s[0], xsum, beta, tau, sc);
-  // u = (1, sc O[1:L, 0]), read for this thread's row p and columns q
-  const double2 up = csel(p == 0, double2{1, 0}, csel(p < L, cmul(sc, c0s[p]), double2{0, 0}));
-  double2 uc[BCU];
-#pragma unroll
-  for (int u = 0; u < BCU; ++u) {
-    const int q = g + BCG * u;
-    uc[u] = csel(q == 0, double2{1, 0}, csel(q < L, cmul(sc, c0s[q]), double2{0, 0}));
-  }
-  if (k > 0) {
-    // z[q] = sum_p conj(u[p]) O[p][q]; O -= conj(tau) u z^T (q >= 1)
-#pragma unroll
-    for (int u = 0; u < BCU; ++u) Ms[p][g + BCG * u] = o[u];
-    __syncthreads();
-    double2 z = {0, 0};  // column p of O over the rows BCR g .. BCR g + BCR - 1
-#pragma unroll
-    for (int a = 0; a < BCR; ++a) {
-      const int pr = BCR * g + a;
-      const double2 upr = csel(pr == 0, double2{1, 0}, csel(pr < L, cmul(sc, c0s[pr]), double2{0, 0}));
-      z = cadd(z, cmulc(upr, Ms[pr][p]));
-    }
-    zp[g][p] = z;
-    __syncthreads();
-    const double2 cu = cmul(cconj(tau), up);
-#pragma unroll
-    for (int u = 0; u < BCU; ++u) {
-      const int q = g + BCG * u;
-      double2 zq = zp[0][q];
-#pragma unroll
-      for (int gg = 1; gg < BCG; ++gg) zq = cadd(zq, zp[gg][q]);
-      o[u] = csel(q == 0, csel(p == 0, double2{beta, 0}, double2{0, 0}), csub(o[u], cmul(cu, zq)));
-    }
-  } else {
-    o[0] = csel(p == 0, double2{beta, 0}, double2{0, 0});
-    if (tid == 0) D.e[i] = beta;
-  }
-  // ---- D <- H^dag D H: y = D u, w = tau y - |tau|^2 (u^dag y) u / 2,
-  //      D -= u w^dag + w u^dag ----
-  double2 y = {0, 0};
-#pragma unroll
-  for (int u = 0; u < BCU; ++u) y = cadd(y, cmul(dm[u], uc[u]));
-  y.x += __shfl_xor(y.x, 32, 64);
-  y.y += __shfl_xor(y.y, 32, 64);
-  if (lane < SBW) part[wv][p] = y;
+  auto publish = [&](int64_t i, int tasks) {
+    __hip_atomic_store(chase_done(D, i), tasks, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  auto wave_sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  auto ticket = [&]() {
+    return __hip_atomic_fetch_add(chase_next(D), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  if (tid == 0) sweep_s = ticket();
   __syncthreads();
-  double2 yp = part[0][p];
+  // A pass of either loop begins and ends at a barrier of the workgroup or the wave:
+  // where it ends in a branch of thread 0 and the next begins with one, the compiler
+  // threads the two and sends the other threads round the loop without thread 0.
+  for (;;) {
+    const int i = sweep_s;
+    if (i > n - 2) return;
+    const int kmax = (int)g_bc_kmax(n, i), kprev = i > 0 ? (int)g_bc_kmax(n, i - 1) : -1;
+    double2 tau = {0, 0};
+    for (int k = 0; k <= kmax; ++k) {
+      const int rk = i + 1 + k * SBW, rp = k > 0 ? rk - SBW : i, L = std::min(SBW, n - rk);
+      const int want = std::min(k + 2, kprev + 1);  // tasks of sweep i - 1 to wait for
+      auto ahead = [&]() {
+        return want <= 0 ? 0
+                         : __hip_atomic_load(chase_done(D, i - 1), __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+      };
+      if (tid == 0) done_s = ahead();
+      __syncthreads();
+      bool owed = k > 0;  // task k - 1 is not published yet
+      if (done_s < want) {
+        if (owed) {  // publish before waiting
+          __builtin_amdgcn_s_waitcnt(0);
+          __syncthreads();
+          if (tid == 0) publish(i, k);
+          owed = false;
+        }
+        if (tid == 0)
+          for (int s = 0; s < CHASE_SPIN && ahead() < want; ++s) __builtin_amdgcn_s_sleep(1);
+        __syncthreads();
+      }
+      // ---- loads, all issued together from in-bounds addresses ----
+      double2 o[BCU], dl[BCU], uq[BCU];
 #pragma unroll
-  for (int w = 1; w < BCT / 64; ++w) yp = cadd(yp, part[w][p]);
-  // gamma = sum_p conj(u[p]) y[p] over the 32 lanes of a half wave (every
-  // half wave holds all p)
-  double gam = cmulc(up, yp).x;
+      for (int u = 0; u < BCU; ++u) {
+        const int q = g + BCG * u;
+        o[u] = band_ld(band + (k > 0 ? int64_t(rp + q) * LDB + SBW + p - q : int64_t(i) * LDB + 1 + p));
+        // lower triangle of D (q <= p), column by column
+        dl[u] = band_ld(band + int64_t(std::min(rk + q, n - 1)) * LDB + (p >= q ? p - q : 0));
+      }
 #pragma unroll
-  for (int o_ = 16; o_ > 0; o_ >>= 1) gam += __shfl_xor(gam, o_, 64);
-  const double t2 = tau.x * tau.x + tau.y * tau.y;
-  const double2 wp = csub(cmul(tau, yp), cscale(0.5 * t2 * gam, up));
+      for (int u = 0; u < BCU; ++u) uq[u] = us[g + BCG * u];
 #pragma unroll
-  for (int u = 0; u < BCU; ++u) {
-    const int q = g + BCG * u;
-    double2 yq = part[0][q];
+      for (int u = 0; u < BCU; ++u) {
+        const int q = g + BCG * u;
+        o[u] = csel(p < L && (k > 0 || q == 0), o[u], double2{0, 0});
+        dl[u] = csel(p < L && q <= p, dl[u], double2{0, 0});
+        if (q == p) dl[u].y = 0;
+        if (q <= p) {  // the entry and its mirror; upper positions are the mirrors' owners'
+          Ms[p][q] = dl[u];
+          Ms[q][p] = cconj(dl[u]);
+        }
+      }
+      // part w of M x: rows of x q = 2 w, 2 w + 1 and 16 further (wave w % 4)
+      auto parts = [&](const double2 (&m)[BCU], const double2 (&x)[BCU]) {
 #pragma unroll
-    for (int w = 1; w < BCT / 64; ++w) yq = cadd(yq, part[w][q]);
-    const double2 wq = csub(cmul(tau, yq), cscale(0.5 * t2 * gam, uc[u]));
-    dm[u] = csub(dm[u], cadd(cmul(up, cconj(wq)), cmul(wp, cconj(uc[u]))));
-    if (q == p) dm[u].y = 0;
+        for (int h = 0; h < 2; ++h) {
+          double2 y = {0, 0};
+          y = cadd(y, cmul(m[h], x[h]));
+          y = cadd(y, cmul(m[h + 2], x[h + 2]));
+          y.x += __shfl_xor(y.x, 32, 64);
+          y.y += __shfl_xor(y.y, 32, 64);
+          if (lane < SBW) part[wv + NW * h][p] = y;
+        }
+      };
+      auto total = [&]() {
+        double2 y = part[0][p];
+#pragma unroll
+        for (int w = 1; w < NP; ++w) y = cadd(y, part[w][p]);
+        return y;
+      };
+      if (k > 0) parts(o, uq);
+      __builtin_amdgcn_s_waitcnt(0);  // the words of task k - 1 are complete
+      __syncthreads();                // Ms (D in full) and the partial sums of O u
+      if (owed && tid == 0) publish(i, k);
+      double2 dm[BCU];
+#pragma unroll
+      for (int u = 0; u < BCU; ++u) dm[u] = Ms[p][g + BCG * u];
+      // ---- k > 0: O <- O (I - tau u u^dag) ----
+      if (k > 0) {
+        const double2 ty = cmul(tau, total());
+#pragma unroll
+        for (int u = 0; u < BCU; ++u) o[u] = csub(o[u], cmul(ty, cconj(uq[u])));
+      }
+      // ---- new reflector from column 0 (held by the threads with g = 0, u = 0) ----
+      if (wv == 0) {
+        if (g == 0) c0s[p] = o[0];
+        const double xs =
+            bfly32(g == 0 && p >= 1 && p < L ? o[0].x * o[0].x + o[0].y * o[0].y : 0.0);
+        if (tid == 0) xsum = xs;
+      }
+      __syncthreads();  // c0s, xsum; the reads of Ms, part and us are done
+      double beta;
+      double2 sc;
+      fast_householder(c0s[0], xsum, beta, tau, sc);
+      // u = (1, sc O[1:L, 0]), read for this thread's row p and columns q
+      const double2 up = csel(p == 0, double2{1, 0}, csel(p < L, cmul(sc, c0s[p]), double2{0, 0}));
+      double2 uc[BCU];
+#pragma unroll
+      for (int u = 0; u < BCU; ++u) {
+        const int q = g + BCG * u;
+        uc[u] = csel(q == 0, double2{1, 0}, csel(q < L, cmul(sc, c0s[q]), double2{0, 0}));
+      }
+      // ---- D: y = D u ----
+      parts(dm, uc);
+      if (k > 0) {
+        // z[q] = sum_p conj(u[p]) O[p][q]; O -= conj(tau) u z^T (q >= 1)
+        const int hf = lane / SBW;
+#pragma unroll
+        for (int u = 0; u < BCU; ++u) {
+          double2 t = {fma(up.x, o[u].x, up.y * o[u].y), fma(up.x, o[u].y, -(up.y * o[u].x))};
+          t.x += dppd<DPP_X1>(t.x);
+          t.y += dppd<DPP_X1>(t.y);
+          if (p % 2 == 0) {
+            zp[wv][p / 2][2 * u + hf][0] = t.x;
+            zp[wv][p / 2][2 * u + hf][1] = t.y;
+          }
+        }
+        wave_sync();  // the wave's own LDS words, in order
+        const double *zr = &zp[wv][0][lane % (4 * BCU) / 2][lane % 2];
+        double z = zr[0];
+#pragma unroll
+        for (int a = 1; a < 16; ++a) z += zr[a * 2 * (2 * BCU + 1)];
+        if (lane < 4 * BCU) reinterpret_cast<double *>(zq[wv])[lane] = z;
+        wave_sync();
+        const double2 cu = {KEEP ? fma(tau.x, up.x, tau.y * up.y) : fma(tau.y, up.y, tau.x * up.x),
+                            fma(tau.x, up.y, -(tau.y * up.x))};
+#pragma unroll
+        for (int u = 0; u < BCU; ++u)
+          o[u] = csel(g + BCG * u == 0, csel(p == 0, double2{beta, 0}, double2{0, 0}),
+                      csub(o[u], cmul(cu, zq[wv][2 * u + hf])));
+      } else {
+        o[0] = csel(p == 0, double2{beta, 0}, double2{0, 0});
+        if (tid == 0) D.e[i] = beta;
+      }
+      __syncthreads();  // part
+      // ---- D <- H^dag D H: w = tau y - |tau|^2 (u^dag y) u / 2, D -= u w^dag + w u^dag ----
+      const double2 yp = total();
+      // u^dag y over the 32 lanes of a half-wave (every half-wave holds all p)
+      const double gam = bfly32(cmulc(up, yp).x);
+      const double t2 = fma(tau.x, tau.x, tau.y * tau.y);
+      const double2 wp = csub(cmul(tau, yp), cscale(0.5 * t2 * gam, up));
+#pragma unroll
+      for (int u = 0; u < BCU; ++u) {
+        const int q = g + BCG * u, src = (lane & SBW) | q;
+        const double2 wq = {__shfl(wp.x, src, 64), __shfl(wp.y, src, 64)};
+        dm[u] = csub(dm[u], cadd(cmul(up, cconj(wq)), cmul(wp, cconj(uc[u]))));
+        if (q == p) dm[u].y = 0;
+      }
+      // ---- stores: O (k > 0), column i (k = 0, the threads with q = 0), D ----
+#pragma unroll
+      for (int u = 0; u < BCU; ++u) {
+        const int q = g + BCG * u;
+        if (p < L && (k > 0 || q == 0))
+          band_st(band + (k > 0 ? int64_t(rp + q) * LDB + SBW + p - q : int64_t(i) * LDB + 1 + p),
+                  o[u]);
+        if (q <= p && p < L) band_st(band + int64_t(rk + q) * LDB + p - q, dm[u]);
+      }
+      // ---- the reflector of the next task of this sweep ----
+      if (g == 0) us[p] = up;
+      if (KEEP && g == 0 && p < L)  // kept for the back-transformation; tau in place of u_0 = 1
+        D.rall[g_bc_off(n, i) + k * SBW + p] = csel(p == 0, tau, up);
+      __builtin_amdgcn_wave_barrier();
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (tid == 0) {
+      publish(i, kmax + 1);
+      sweep_s = ticket();
+    }
+    __syncthreads();
   }
-  // ---- stores, all at the end and unconditional: entries without a place
-  // go to the sink.  O (k > 0) rows past the block end lie past row n - 1
-  // of their columns (padding that nothing reads); column i (k = 0) is
-  // written by the threads with q = 0. ----
-  double2 *sk = D.sink + tid % SINK;
-#pragma unroll
-  for (int u = 0; u < BCU; ++u) {
-    const int q = g + BCG * u;
-    double2 *dst = k > 0 ? band + (rp + q) * LDB + SBW + p - q : (q == 0 ? band + i * LDB + 1 + p : sk);
-    *dst = o[u];
-  }
-#pragma unroll
-  for (int u = 0; u < BCU; ++u) {
-    const int q = g + BCG * u;
-    double2 *dst = (q <= p && p < L) ? band + (rk + q) * LDB + p - q : sk;
-    *dst = dm[u];
-  }
-  // ---- the reflector of the next step of this sweep ----
-  if (g == 0) D.rfl[i * SBW + p] = up;
-  if (tid == 0) D.rtau[i] = tau;
-  if (KEEP && g == 0 && p < L)  // kept for the back-transformation; tau in place of u_0 = 1
-    D.rall[g_bc_off(n, i) + k * SBW + p] = csel(p == 0, tau, up);
 }
 
 // d from the band's diagonal
@@ -902,24 +1058,6 @@ __global__ __launch_bounds__(ENT) void k_sb_diag(Desc D) {
 //                   flight together
 // ---------------------------------------------------------------------------
 
-// cross-lane moves within groups of eight lanes (DPP, no LDS round trip):
-// quad_perm [1,0,3,2] (lane ^ 1), [2,3,0,1] (lane ^ 2), [0,0,0,0] (lane 0 of
-// the quad) and row_half_mirror (lane i <-> 7 - i of each eight)
-constexpr int DPP_X1 = 0xB1, DPP_X2 = 0x4E, DPP_Q0 = 0x00, DPP_HM = 0x141;
-template <int CTRL>
-__device__ __forceinline__ double dppd(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_mov_dpp(int(b), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_mov_dpp(int(b >> 32), CTRL, 0xF, 0xF, false);
-  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo));
-}
-// sum over the eight lanes of a group, on every lane: the quad sums by two
-// exchanges, then the mirrored quad's sum
-__device__ __forceinline__ double sum8(double v) {
-  v += dppd<DPP_X1>(v);
-  v += dppd<DPP_X2>(v);
-  return v + dppd<DPP_HM>(v);
-}
 // the value of lane 0 of the group of eight, on every lane (pl: lane in the group)
 __device__ __forceinline__ double bcast8(double v, int pl) {
   const double q = dppd<DPP_Q0>(v);

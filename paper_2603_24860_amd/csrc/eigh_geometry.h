@@ -107,8 +107,8 @@ struct Desc {
   double2 *xp;               // [SBNS][SBW][ldv] split-K partial sums of X = A22 U
   double2 *yrec;             // [nw][SBW][SBW] partial sums of V^dag X
   double2 *band;             // [n][LDB] lower band of the reduced matrix, column by column
-  double2 *rfl;              // [n][SBW] latest reflector of each bulge-chasing sweep
-  double2 *rtau;             // [n] its tau
+  double2 *rfl;              // [n][SBW] its first word: finished tasks of a bulge-chasing sweep
+  double2 *rtau;             // [n] its first word: the next sweep that no workgroup has taken
   double2 *sink;             // [SINK] target of the stores of masked lanes (never read)
   // two-stage reduction with refinement (K > 0): every reflector of both
   // stages, for the back-transformation; null otherwise
@@ -253,7 +253,8 @@ __host__ __device__ __forceinline__ int64_t g_sb_hemm_wgs(int64_t m) {
   return cdiv(m, SBHM) * SBNS;
 }
 // bulge chasing: task (i, k) is step k of sweep i (i = 0 .. n - 2,
-// k = 0 .. (n - 2 - i) / SBW); launch t runs the tasks with 2 i + k = t
+// k = 0 .. (n - 2 - i) / SBW); it can start at t = 2 i + k, when the tasks of
+// sweeps ilo .. ihi run side by side
 __host__ __device__ __forceinline__ int64_t g_bc_kmax(int64_t n, int64_t i) {
   return (n - 2 - i) / SBW;
 }

@@ -69,41 +69,6 @@ __device__ __forceinline__ double2 xget(const u64 *p) {
 }
 __device__ __forceinline__ void wait_stores() { __builtin_amdgcn_s_waitcnt(0); }
 
-// sums over 16, 32 and 64 lanes, on every lane: DPP moves within a row of 16
-// (a few cycles each), LDS permutes only across rows
-__device__ __forceinline__ double pan_sum16(double v) {
-  v = sum8(v);
-  return v + dppd<0x140>(v);  // row_mirror: lane i <-> 15 - i
-}
-__device__ __forceinline__ double pan_sum32(double v) {
-  v = pan_sum16(v);
-  return v + __shfl_xor(v, 16, 64);
-}
-__device__ __forceinline__ double pan_sum64(double v) {
-  v = pan_sum32(v);
-  return v + __shfl_xor(v, 32, 64);
-}
-
-// `householder` (LAPACK zlarfg semantics) with one reciprocal square root and one
-// reciprocal, each with two Newton steps, instead of a square root and four
-// divisions: it sits on the chain of every column.
-__device__ __forceinline__ void pan_householder(double2 al, double xn2, double &beta, double2 &tau,
-                                                double2 &scale) {
-  tau = scale = double2{0, 0};
-  beta = al.x;
-  if (xn2 == 0.0 && al.y == 0.0) return;
-  const double q = al.x * al.x + al.y * al.y + xn2;
-  double r = __builtin_amdgcn_rsq(q);
-  r = fma(r * 0.5, fma(-q * r, r, 1.0), r);
-  r = fma(r * 0.5, fma(-q * r, r, 1.0), r);
-  const double nrm = q * r, sg = al.x >= 0 ? -1.0 : 1.0;
-  beta = sg * nrm;
-  tau = double2{(beta - al.x) * (sg * r), -al.y * (sg * r)};
-  const double2 den = {al.x - beta, al.y};
-  const double id = rcp64(den.x * den.x + den.y * den.y);
-  scale = double2{den.x * id, -den.y * id};
-}
-
 // The exchange buffers of a block, carved from D.px (words); entries are complex.
 struct PanX {
   u64 *col, *rec, *pa, *bred, *head, *yj;  // one ring slot each, see slot()
@@ -237,14 +202,14 @@ __device__ __forceinline__ void b_panel(const Desc &D, int j0, int g0) {
           }
         }
       }
-      s1 = pan_sum64(s1);
+      s1 = sum64(s1);
       if (lane == 0) sh[wv] = s1;
       __syncthreads();  // sh, vs, hs
       double S1 = sh[0];
 #pragma unroll
       for (int w = 1; w < ENT / 64; ++w) S1 += sh[w];
       double beta;
-      pan_householder(vs[m0 - j0], S1, beta, tau, sc);
+      fast_householder(vs[m0 - j0], S1, beta, tau, sc);
       // the records of this wave's first dot product (published after the column):
       // on their way during the product with A, which does not need them
       const int s0 = g + G * wv;
@@ -287,8 +252,8 @@ __device__ __forceinline__ void b_panel(const Desc &D, int j0, int g0) {
         }
 #pragma unroll
         for (int k = 0; k < WR; ++k) {
-          sr[k] = pan_sum64(sr[k]);
-          si[k] = pan_sum64(si[k]);
+          sr[k] = sum64(sr[k]);
+          si[k] = sum64(si[k]);
           const int rr = wv + (ENT / 64) * k;
           if (lane == 0 && rr < RWM) {
             const int r = rb + rr;
@@ -325,8 +290,8 @@ __device__ __forceinline__ void b_panel(const Desc &D, int j0, int g0) {
 #pragma unroll
         for (int u = 0; u < 4; ++u)
           if (lane + 64 * u < G) x = cadd(x, xval(ra[u], rc[u]));
-        x.x = pan_sum64(x.x);
-        x.y = pan_sum64(x.y);
+        x.x = sum64(x.x);
+        x.y = sum64(x.y);
         if (lane == 0) xput(X.bred + 2 * s, x);
       }
       __syncthreads();  // ysh, vsh, prod
@@ -385,8 +350,8 @@ __device__ __forceinline__ void b_panel(const Desc &D, int j0, int g0) {
         if (tid == ENT - 1) yjs = xval(c, d);
       }
       wait_stores();  // the XNONE stores of column i - 1, before anything of column i + 1 goes out
-      pv.x = pan_sum64(pv.x);
-      pv.y = pan_sum64(pv.y);
+      pv.x = sum64(pv.x);
+      pv.y = sum64(pv.y);
       if (lane == 0) {
         sh2[2 * wv] = pv.x;
         sh2[2 * wv + 1] = pv.y;
@@ -419,12 +384,12 @@ __device__ __forceinline__ void b_panel(const Desc &D, int j0, int g0) {
         t1[h] = cadd(cmul(vl, q), cmul(wl, p));
         t2[h] = cadd(cmul(vl, cconj(wh)), cmul(wl, cconj(vh)));
       }
-      pq = pan_sum32(pq);
-      sj = double2{pan_sum32(sj.x), pan_sum32(sj.y)};
+      pq = sum32(pq);
+      sj = double2{sum32(sj.x), sum32(sj.y)};
 #pragma unroll
       for (int h = 0; h < HR; ++h) {
-        t1[h] = double2{pan_sum32(t1[h].x), pan_sum32(t1[h].y)};
-        t2[h] = double2{pan_sum32(t2[h].x), pan_sum32(t2[h].y)};
+        t1[h] = double2{sum32(t1[h].x), sum32(t1[h].y)};
+        t2[h] = double2{sum32(t2[h].x), sum32(t2[h].y)};
       }
       const double2 wdv = cmulc(tau, double2{pv.x - 2 * pq, pv.y});
       const double2 al = cmul(double2{-0.5 * tau.x, -0.5 * tau.y}, wdv);

@@ -131,3 +131,26 @@ def test_captured_panels():
         graph.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(o, r) for o, r in zip(out, ref))
+
+
+@pytest.mark.parametrize("scale", [1e-153, 1e-147, 1e-139])
+@pytest.mark.parametrize("two_stage", [False, True])
+def test_reflectors_near_underflow(two_stage, scale):
+    """Couplings whose squares are denormal or barely normal: the reflectors of the
+    panels and of the chase take the sequence without reciprocal estimates there."""
+    from paper_2603_24860_amd import bse as B
+    n = 140
+    print("[gpu-case] tiny couplings", two_stage, scale, flush=True)
+    g = np.random.default_rng(7)
+    lam = np.sort(g.uniform(-1, 1, n))
+    a = g.normal(size=(n, n)) + 1j * g.normal(size=(n, n))
+    a = np.diag(lam).astype(complex) + scale * (a + a.conj().T)
+    a, b = torch.from_numpy(a).cuda(), torch.from_numpy(g.normal(size=n) + 0j).cuda()
+    nmin = B.bse_block_eigh_set_two_stage(2 if two_stage else 4096)
+    try:
+        run, out = _solver(B, a, b, B.FP64)
+        run()
+        torch.cuda.synchronize()
+    finally:
+        B.bse_block_eigh_set_two_stage(nmin)
+    assert np.abs(out[0].cpu().numpy() - lam).max() <= 1e-11
