@@ -27,6 +27,7 @@
 // dependent launch per step, bound by reading H_mu once (HBM or, for blocks
 // that fit, the last-level cache).
 //   k_hd_step      one Lanczos step (grid: one workgroup per 4 RPW rows)
+//   k_hd_step_s    the same for FP32 blocks whose rows fit the registers
 //   k_hd_finish    a_{K-1}, b_{K-1} and the last residual norm b_K
 //   k_hd_spectrum  one thread per frequency: both continued fractions
 #include <hip/hip_runtime.h>
@@ -271,6 +272,149 @@ __global__ __launch_bounds__(HNT) void k_hd_step(int64_t n, const TH *__restrict
   }
 }
 
+// The same step for FP32 blocks of up to 2304 columns (pairs as in VEC): about one
+// workgroup per CU, so the latency of a step bounds it (launch, partial sums,
+// vectors, rows, one after the other), not bandwidth, and registers cost nothing.
+// Everything the step reads is requested first: the partial sums, the three vectors
+// and most of the wave's rows of H_mu are on their way while the coefficients are
+// formed, the rest of the rows once the vectors have left their registers; one LDS
+// chunk holds the whole vector.  Every sum has the order of k_hd_step.  2304
+// columns are what the registers of two workgroups per CU hold (n > 2048 has more
+// workgroups than CUs); blocks of up to 768 take a form without the loads past
+// them (n = 604: 7.8 us a step with them).  us a step, k_hd_step -> here:
+// n = 120 6.1 -> 5.8, 604 7.6 -> 6.2, 1500 10.4 -> 8.5, 2160 16.5 -> 13.2.
+constexpr int HSN = 2304;  // and HSN / 3 for blocks up to that
+template <int HSN>
+__global__ __launch_bounds__(HNT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_hd_step_s(
+    int n, const float2 *__restrict__ H, int64_t ld, const double2 *__restrict__ Bv, int j, int G,
+    double2 *__restrict__ P, double2 *__restrict__ Y, double *__restrict__ part,
+    double *__restrict__ a, double *__restrict__ b) {
+  constexpr int RPW = 2;
+  constexpr int HSS = HSN / 128;           // column pairs per lane
+  constexpr int HSX = HSN / HNT;           // vector entries per thread
+  constexpr int HSP = HSS < 12 ? HSS : 12; // pairs requested before the coefficients
+  __shared__ double2 xs[HSN];
+  __shared__ double red[3][HWV];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const double2 *Pm1 = j == 0 ? Bv : P + int64_t((j + 2) % 3) * n;
+  const double2 *Pm2 = j < 2 ? Bv : P + int64_t((j + 1) % 3) * n;
+  double2 *Pj = P + int64_t(j % 3) * n;
+  const double2 *Ym1 = j == 0 ? Bv : Y + int64_t((j + 1) & 1) * n;
+  double2 *Yj = Y + int64_t(j & 1) * n;
+  double *pout = part + int64_t(j & 1) * 3 * G;
+
+  double2 y[HSX], p[HSX], q[HSX];
+#pragma unroll
+  for (int t = 0; t < HSX; ++t) {
+    const int i = min(tid + HNT * t, n - 1);
+    y[t] = Ym1[i];
+    p[t] = Pm1[i];
+    q[t] = Pm2[i];
+  }
+  const int r0 = (int(blockIdx.x) * HWV + wv) * RPW;
+  const int ce = (n - 2) & ~1;  // the last pair inside every row
+  float4 h[RPW][HSS];
+  float2 hl[RPW];  // the last column, alone in its pair if n is odd
+  double2 qr[RPW];
+  const float2 *row[RPW];
+#pragma unroll
+  for (int r = 0; r < RPW; ++r) {
+    row[r] = H + int64_t(min(r0 + r, n - 1)) * ld;
+#pragma unroll
+    for (int m = 0; m < HSP; ++m)
+      h[r][m] = *reinterpret_cast<const float4 *>(row[r] + min(2 * lane + 128 * m, ce));
+  }
+  Coef c{0, 0, 0, 0, 0};
+  if (j > 0) {
+    c = hd_coef(j, G, part + int64_t((j + 1) & 1) * 3 * G, b, red);
+    if (blockIdx.x == 0 && tid == 0) {
+      a[j - 1] = c.alpha;
+      b[j - 1] = c.bj1;
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < HSX; ++t) {
+    const int i = tid + HNT * t;
+    double2 x = y[t];  // j = 0: B_mu
+    if (j > 0) {
+      x = make_double2(c.cy * y[t].x + c.cp * p[t].x, c.cy * y[t].y + c.cp * p[t].y);
+      if (j >= 2) {
+        x.x += c.cq * q[t].x;
+        x.y += c.cq * q[t].y;
+      }
+    }
+    if (i < n) xs[i] = x;
+  }
+#pragma unroll
+  for (int r = 0; r < RPW; ++r) {
+#pragma unroll
+    for (int m = HSP; m < HSS; ++m)
+      h[r][m] = *reinterpret_cast<const float4 *>(row[r] + min(2 * lane + 128 * m, ce));
+    hl[r] = row[r][n - 1];
+    qr[r] = Pm1[min(r0 + r, n - 1)];
+  }
+  __syncthreads();
+  double2 acc[RPW];
+#pragma unroll
+  for (int r = 0; r < RPW; ++r) acc[r] = make_double2(0.0, 0.0);
+#pragma unroll
+  for (int m = 0; m < HSS; ++m) {
+    const int cc = 2 * lane + 128 * m;
+    if (cc + 1 < n) {
+      const double2 x0 = xs[cc], x1 = xs[cc + 1];
+#pragma unroll
+      for (int r = 0; r < RPW; ++r) {
+        const double hr0 = h[r][m].x, hi0 = h[r][m].y, hr1 = h[r][m].z, hi1 = h[r][m].w;
+        acc[r].x += hr0 * x0.x - hi0 * x0.y;
+        acc[r].y += hr0 * x0.y + hi0 * x0.x;
+        acc[r].x += hr1 * x1.x - hi1 * x1.y;
+        acc[r].y += hr1 * x1.y + hi1 * x1.x;
+      }
+    }
+  }
+  if ((n & 1) && lane == ((n - 1) / 2) % 64) {
+    const double2 x = xs[n - 1];
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) {
+      const double2 g = make_double2(double(hl[r].x), double(hl[r].y));
+      acc[r].x += g.x * x.x - g.y * x.y;
+      acc[r].y += g.x * x.y + g.y * x.x;
+    }
+  }
+  double pp = 0, py = 0, pq = 0;
+  double2 xo[RPW], yo[RPW];
+#pragma unroll
+  for (int r = 0; r < RPW; ++r) {
+    const double yx = wsum(acc[r].x), yy = wsum(acc[r].y);
+    const int i = r0 + r;
+    xo[r] = yo[r] = make_double2(0.0, 0.0);
+    if (lane == 0 && i < n) {
+      const double2 x = xs[i];
+      xo[r] = x;
+      yo[r] = make_double2(yx, yy);
+      pp += x.x * x.x + x.y * x.y;
+      py += x.x * yx + x.y * yy;
+      if (j > 0) pq += x.x * qr[r].x + x.y * qr[r].y;
+    }
+  }
+  block_sum3(pp, py, pq, red);
+  if (lane == 0) {
+#pragma unroll
+    for (int r = 0; r < RPW; ++r) {
+      const int i = r0 + r;
+      if (i < n) {
+        Pj[i] = xo[r];
+        Yj[i] = yo[r];
+      }
+    }
+  }
+  if (tid == 0) {
+    pout[blockIdx.x] = pp;
+    pout[G + blockIdx.x] = py;
+    pout[2 * G + blockIdx.x] = pq;
+  }
+}
+
 // One workgroup: a_{K-1}, b_{K-1} from the last step's partials, then the norm
 // of the last residual P_K into b_K.
 __global__ __launch_bounds__(HNT) void k_hd_finish(int64_t n, int K, int G,
@@ -337,6 +481,14 @@ void launch_steps(int64_t n, const TH *H, int64_t ld, const double2 *Bv, int K, 
                   double2 *P, double2 *Y, double *part, double *a, double *b, hipStream_t s) {
   if constexpr (std::is_same<TH, float2>::value) {
     if (ld % 2 == 0 && reinterpret_cast<uintptr_t>(H) % 16 == 0) {
+      if constexpr (RPW == 2)
+        if (n >= 2 && n <= HSN) {
+          const auto step = n <= HSN / 3 ? k_hd_step_s<HSN / 3> : k_hd_step_s<HSN>;
+          for (int j = 0; j < K; ++j)
+            BSE_LAUNCH("k_hd_step", step, dim3(G), dim3(HNT), 0, s, int(n), H, ld, Bv, j, G, P, Y,
+                       part, a, b);
+          return;
+        }
       for (int j = 0; j < K; ++j)
         BSE_LAUNCH("k_hd_step", (k_hd_step<TH, RPW, true>), dim3(G), dim3(HNT), 0, s, n, H, ld,
                    Bv, j, G, P, Y, part, a, b);
