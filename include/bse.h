@@ -217,8 +217,7 @@ int32_t bse_build(const bse_problem *p, int32_t prec, void *H, int64_t ldh, void
  *                   BSE_EINVAL (unknown plan, NULL block arrays), BSE_ESHAPE
  *                   (ldmu < n), BSE_EUNSUPPORTED (nv nc too large).
  *   bse_seed_free   forgets the plan.
- * Precision FP32 or FP64; shapes as the fused direct kernel (Nmb = 64 m with
- * m <= 6, nv <= 4, nc <= 6), else BSE_EUNSUPPORTED.
+ * Precision FP32 or FP64; shapes Nmb = 64 m with m <= 6, nv <= 4, nc <= 6, else BSE_EUNSUPPORTED.
  * ------------------------------------------------------------------------- */
 size_t bse_seed_ws(int32_t group, const bse_problem *p, int32_t prec);
 int32_t bse_seed_plan(int32_t group, const bse_problem *p, int32_t prec, void *ws,
@@ -284,6 +283,9 @@ int32_t bse_dipole_weights(const bse_problem *p, const void *B, int32_t nblk,
  * padded with zero strength.  Hmu is read only.
  * prec: FP64 (all FP64), FP32 (FP32 storage of the working copy, its HEMV
  * and trailing updates; FP64 panel vectors, scalars and tridiagonal step).
+ * FP64 storage reduces each panel of up to 2304 trailing rows in one launch whose
+ * workgroups wait for one another; where they cannot all be on the device within
+ * 20 ms (other work holds it), one of them does the panel, with the same results.
  * The HEMV of trailing blocks above 2048 rows reads only their lower half;
  * its partial sums take up to max(49, (n + 63) / 256) x n x 16 B more
  * workspace (n > 2049).
@@ -366,7 +368,8 @@ int32_t bse_block_eigh_status(int64_t n, int32_t prec, int32_t nrefine, const vo
  * hipMalloc, hipFree or allocating library call is made.  That fits, for
  * example, FP32 blocks up to n = 3900 without refinement and up to n = 1500
  * with nrefine = 100 (the limit is the one-stage bse_block_eigh_ws(n, ...) <=
-the maximum: this solver always takes the one-stage reduction).
+ * the maximum, the exchange words of FP64 panels not counted: they have 2 MiB of
+ * their own; this solver always takes the one-stage reduction).
  * No part of the array needs to start at zero: every word a kernel reads was
  * written earlier in the same call.
  * The first call on a device looks up the array's device address (the
