@@ -395,15 +395,18 @@ ProjBlk proj_blk(const bse_block &b, void *Hmu, int64_t ldmu, double2 *Bmu) {
 
 // Bands per workgroup: as many as leave PWGS workgroups (the tables of a
 // workgroup are three dependent loads; 8^3 with 4 + 4 bands: 182 us, 196 with
-// 20000 and 213 with 4096 workgroups).
-constexpr int PWGS = 8192;
+// 20000 and 213 with 4096 workgroups), but few: the rows of many bands in turn keep
+// workgroups side by side from reading the same stretch of H (12^3, 4 + 6 bands:
+// 4.8 ms with at most 6, 5.1 with 8, 8.4 with 15, 4.9 with 1; 5.6 for a whole row
+// of H at a time through LDS; 10^3: 0.76 ms, 1.07).
+constexpr int PWGS = 8192, PBPW = 6;
 template <typename T, bool SEEDSRC>
 int32_t launch_project(const char *name, const bse_problem *p, const void *H, int64_t ldh,
                        const ProjList &L, const SeedSrc &sd, const double2 *B, hipStream_t s) {
   const int nb = p->nv * p->nc;
   const size_t lds = PMAXL * nb > PNT ? sizeof(double2) * PMAXR * PMAXR * nb : 0;
   const int64_t wgs = int64_t(p->nkorb) * p->nkorb * nb * L.n;
-  const int bpw = int(std::max<int64_t>(1, std::min<int64_t>(nb, wgs / PWGS)));
+  const int bpw = int(std::max<int64_t>(1, std::min<int64_t>(std::min(nb, PBPW), wgs / PWGS)));
   const dim3 g((unsigned)((nb + bpw - 1) / bpw * L.n), (unsigned)p->nkorb, (unsigned)p->nkorb);
   BSE_LAUNCH(name, (k_project<T, SEEDSRC>), g, dim3(PNT), lds, s, p->nv, p->nc, (const T *)H, ldh, L,
              sd, B, bpw);
