@@ -34,8 +34,10 @@ constexpr int PNT = 256;     // threads per workgroup
 constexpr int PMAXR = 9;     // basis vectors per orbit: d_mu m_mu(O) <= d_max^2
 constexpr int PMAXL = 48;    // orbit size <= |S|
 constexpr int PMAXB = 12;    // blocks per launch
-// rows of H in flight per thread (FP32: 182 us with 8, 197 with 4, 205 with 12)
-template <typename T> constexpr int PU_OF = sizeof(T) == 4 ? 8 : 4;
+// rows in flight per thread: of H in FP32 8 (182 us, 197 with 4, 205 with 12); from
+// the seed pieces 4, where 8 take the registers of a wave (12 x 12 x 1, 4 + 6 bands:
+// 122 us, 141 with 8)
+template <typename T, bool SEEDSRC> constexpr int PU_OF = sizeof(T) == 4 && !SEEDSRC ? 8 : 4;
 
 // One block of a launch (device pointers as in bse_block; Bmu may be NULL).
 struct ProjBlk {
@@ -117,6 +119,7 @@ __device__ __forceinline__ int64_t uni(int64_t x) {
 // is loaded once per column; the diagonal term only where O is O' (diag).
 template <typename T, bool SEEDSRC, bool ONEX> struct ProjSrc {
   typedef typename std::conditional<sizeof(T) == 4, float2, double2>::type C2;
+  static constexpr int PU = PU_OF<T, false>;
   struct Raw {
     C2 a;
   };
@@ -128,6 +131,7 @@ template <typename T, bool SEEDSRC, bool ONEX> struct ProjSrc {
 };
 template <typename T, bool ONEX> struct ProjSrc<T, true, ONEX> {
   typedef typename std::conditional<sizeof(T) == 4, float2, double2>::type C2;
+  static constexpr int PU = PU_OF<T, true>;
   struct Raw {
     C2 d, x;
   };
@@ -159,7 +163,7 @@ template <typename T, bool ONEX> struct ProjSrc<T, true, ONEX> {
 template <typename T, int R, bool GEN, typename Src>
 __device__ __forceinline__ void proj_stage1(const Src &S, const SeedSrc &sd, ConstD u1, int r1,
                                             int L1, bool work, double2 (&y)[PMAXR]) {
-  constexpr int PU = PU_OF<T>;
+  constexpr int PU = Src::PU;
   double ar[R], ai[R];
 #pragma unroll
   for (int j = 0; j < R; ++j) ar[j] = ai[j] = 0.0;
@@ -206,12 +210,17 @@ __device__ __forceinline__ void proj_stage1(const Src &S, const SeedSrc &sd, Con
     default: proj_stage1<T, 9, true>(S, sd, u1, r1, L1, work, y);                \
   }
 
-// outs (dynamic LDS): [r1][r2 nb] sums over the column tiles, where there are several.
+// outs (dynamic LDS): [r1][r2 wb] sums over the column tiles, where there are several.
+// SPLIT: the column bands b' in parts of wcol (the last may be smaller), one workgroup
+// each, so that outs leaves room for the workgroups that hide the latency of a tile
+// (36 bands: 47 KB of outs, two workgroups on a compute unit) and small orbits fit
+// one tile.  Where: proj_parts.
 constexpr int PRG = 3;  // vectors of y staged at a time (9: 271 us instead of 182)
-template <typename T, bool SEEDSRC>
-__global__ __launch_bounds__(PNT) void k_project(int nv, int nc, const T *__restrict__ H,
-                                                    int64_t ldh, ProjList P, SeedSrc sd,
-                                                    const double2 *__restrict__ B, int bpw) {
+template <typename T, bool SEEDSRC, bool SPLIT>
+__global__ __launch_bounds__(PNT)
+__attribute__((amdgpu_waves_per_eu(SEEDSRC && SPLIT ? 3 : 1, 8))) void k_project(
+    int nv, int nc, const T *__restrict__ H, int64_t ldh, ProjList P, SeedSrc sd,
+    const double2 *__restrict__ B, int bpw, int wcol) {
   typedef typename std::conditional<sizeof(T) == 4, float2, double2>::type C2;
   extern __shared__ __attribute__((aligned(16))) unsigned char plds[];
   __shared__ double2 ys[PRG * PNT];
@@ -223,11 +232,14 @@ __global__ __launch_bounds__(PNT) void k_project(int nv, int nc, const T *__rest
   const int tid = threadIdx.x, nb = nv * nc;
   double2 *outs = reinterpret_cast<double2 *>(plds);
   const ProjBlk &K = P.b[blockIdx.x % P.n];
-  const int band0 = int(blockIdx.x / P.n) * bpw;  // first (v, c) of the output rows
+  const int ncol = SPLIT ? (nb + wcol - 1) / wcol : 1;  // parts of the column bands
+  const int xp = int(blockIdx.x / P.n), c0 = SPLIT ? xp % ncol * wcol : 0;
+  const int wb = SPLIT ? std::min(wcol, nb - c0) : nb;  // this part: bands c0 .. c0 + wb - 1
+  const int band0 = xp / ncol * bpw;                    // first (v, c) of the output rows
   // orbit ids grow with orbit size on the simple grids, so the largest (longest)
   // orbit pairs are dispatched first and do not form a tail
   const int o2 = gridDim.y - 1 - blockIdx.y, o1 = gridDim.z - 1 - blockIdx.z;
-  if (K.Bmu && band0 == 0 && o1 == o2) project_vec(K, o1, nb, B);
+  if (K.Bmu && xp == 0 && o1 == o2) project_vec(K, o1, nb, B);
   const int r1 = uni(K.orb_dim[o1]), r2 = uni(K.orb_dim[o2]);
   const int a1 = uni(K.mem_off[o1]), a2 = uni(K.mem_off[o2]);
   const int L1 = uni(K.mem_off[o1 + 1]) - a1, L2 = uni(K.mem_off[o2 + 1]) - a2;
@@ -254,7 +266,7 @@ __global__ __launch_bounds__(PNT) void k_project(int nv, int nc, const T *__rest
   else
     __syncthreads();
   const ConstD u1 = (ConstD)(uintptr_t)(K.ub + v1);
-  const int per = L2 * nb, oc = r2 * nb;
+  const int per = L2 * wb, oc = r2 * wb;
   // columns go to the threads in whole waves; where they take at most half of
   // them, several bands run side by side (a wave has one band)
   const int pad = std::min(nt, (per + 63) / 64 * 64), bc = nt / pad;
@@ -263,7 +275,7 @@ __global__ __launch_bounds__(PNT) void k_project(int nv, int nc, const T *__rest
     const int nbd = std::min(bc, bend - bb);  // bands of this round
     const int band = std::min(bb + bl, bend - 1);
     for (int t0 = 0; t0 < per; t0 += nt) {
-      const int col = t0 + ct, cc = std::min(col, per - 1), i2 = cc / nb, b2 = cc % nb;
+      const int col = t0 + ct, cc = std::min(col, per - 1), i2 = cc / wb, b2 = c0 + cc % wb;
       const bool work = col < per && bl < nbd;
       double2 y[PMAXR];
       if constexpr (SEEDSRC) {
@@ -299,15 +311,15 @@ __global__ __launch_bounds__(PNT) void k_project(int nv, int nc, const T *__rest
         __syncthreads();
         const int nq = std::min(PRG, r1 - g);
         for (int e = tid; e < nbd * nq * oc; e += nt) {
-          const int f = e % oc, qb = e / oc, q = qb % nq, eb = qb / nq, j2 = f / nb, bq = f % nb;
+          const int f = e % oc, qb = e / oc, q = qb % nq, eb = qb / nq, j2 = f / wb, bq = f % wb;
           double zr = 0, zi = 0;
           // members whose entry (k', bq) lies in this tile
-          const int ia = t0 > bq ? (t0 - bq + nb - 1) / nb : 0;
-          const int ib = std::min(L2, (t0 + cn - bq + nb - 1) / nb);
+          const int ia = t0 > bq ? (t0 - bq + wb - 1) / wb : 0;
+          const int ib = std::min(L2, (t0 + cn - bq + wb - 1) / wb);
           const double2 *yp = ys + q * nt + eb * pad + bq - t0;
 #pragma unroll 4
           for (int k2 = ia; k2 < ib; ++k2) {
-            const double2 yv = yp[k2 * nb];
+            const double2 yv = yp[k2 * wb];
             const double w = u2s[k2 * r2 + j2];
             zr += w * yv.x;
             zi += w * yv.y;
@@ -321,8 +333,8 @@ __global__ __launch_bounds__(PNT) void k_project(int nv, int nc, const T *__rest
             z = double2{zr, zi};
           }
           if (last)
-            reinterpret_cast<C2 *>(K.Hmu)[(q1 + bb + eb + int64_t(g + q) * nb) * K.ldmu + q2 + f] =
-                C2{T(zr), T(zi)};
+            reinterpret_cast<C2 *>(K.Hmu)[(q1 + bb + eb + int64_t(g + q) * nb) * K.ldmu + q2 +
+                                          j2 * nb + c0 + bq] = C2{T(zr), T(zi)};
         }
       }
     }
@@ -400,16 +412,40 @@ ProjBlk proj_blk(const bse_block &b, void *Hmu, int64_t ldmu, double2 *Bmu) {
 // 4.8 ms with at most 6, 5.1 with 8, 8.4 with 15, 4.9 with 1; 5.6 for a whole row
 // of H at a time through LDS; 10^3: 0.76 ms, 1.07).
 constexpr int PWGS = 8192, PBPW = 6;
+
+// Parts of the column bands (SPLIT), where the larger orbits outgrow a tile of PNT
+// columns and outs takes half of the LDS: from 19 bands on two, but only where most
+// orbits have more than the 12 members of a layered group (12 times 21 bands fit); from
+// 22 on three (8 to 11 bands: 64 B runs at 24); from 33 on two (17 to 21: parts of 9
+// or 12 read H in pieces too short).  FP32 us with one, two, three parts: 10^3, 18 bands
+// 1364, 1359, 1590, 20 bands 1863, 1648, 2286; 24 x 24 x 1, 20 bands 619, 637, 807, 24
+// bands 1067, 942, 850; 8^3, 30 bands 1325, 1034, 908, 36 bands 2110, 1270, 1344; 20 x
+// 20 x 1, 36 bands, all blocks 4897, 3120, 4254, 3734 with four.  Calls of fewer
+// workgroups than PWGS have room anyway and pay for the tables of each part (4^3, 30
+// bands: 33, 29, 38).  The rule does not look at the number of blocks: a block's sums
+// are the same in any company.
+int proj_parts(const bse_problem *p) {
+  const int nb = p->nv * p->nc;
+  if (nb <= 18 || int64_t(p->nkorb) * p->nkorb * nb < PWGS) return 1;
+  if (nb <= 21) return int64_t(p->grid[0]) * p->grid[1] * p->grid[2] > 12 * int64_t(p->nkorb) ? 2 : 1;
+  return nb <= 32 ? 3 : 2;
+}
+
 template <typename T, bool SEEDSRC>
 int32_t launch_project(const char *name, const bse_problem *p, const void *H, int64_t ldh,
                        const ProjList &L, const SeedSrc &sd, const double2 *B, hipStream_t s) {
   const int nb = p->nv * p->nc;
-  const size_t lds = PMAXL * nb > PNT ? sizeof(double2) * PMAXR * PMAXR * nb : 0;
-  const int64_t wgs = int64_t(p->nkorb) * p->nkorb * nb * L.n;
+  const int parts = proj_parts(p), wcol = (nb + parts - 1) / parts;
+  const int64_t wgs = int64_t(p->nkorb) * p->nkorb * nb * parts * L.n;
+  const size_t lds = PMAXL * wcol > PNT ? sizeof(double2) * PMAXR * PMAXR * wcol : 0;
   const int bpw = int(std::max<int64_t>(1, std::min<int64_t>(std::min(nb, PBPW), wgs / PWGS)));
-  const dim3 g((unsigned)((nb + bpw - 1) / bpw * L.n), (unsigned)p->nkorb, (unsigned)p->nkorb);
-  BSE_LAUNCH(name, (k_project<T, SEEDSRC>), g, dim3(PNT), lds, s, p->nv, p->nc, (const T *)H, ldh, L,
-             sd, B, bpw);
+  const dim3 g((unsigned)((nb + bpw - 1) / bpw * parts * L.n), (unsigned)p->nkorb, (unsigned)p->nkorb);
+  if (parts > 1)
+    BSE_LAUNCH(name, (k_project<T, SEEDSRC, true>), g, dim3(PNT), lds, s, p->nv, p->nc,
+               (const T *)H, ldh, L, sd, B, bpw, wcol);
+  else
+    BSE_LAUNCH(name, (k_project<T, SEEDSRC, false>), g, dim3(PNT), lds, s, p->nv, p->nc,
+               (const T *)H, ldh, L, sd, B, bpw, wcol);
   BSE_HIP_CHECK(hipGetLastError());
   return BSE_OK;
 }
