@@ -286,6 +286,8 @@ int32_t bse_dipole_weights(const bse_problem *p, const void *B, int32_t nblk,
  * FP64 storage reduces each panel of up to 2304 trailing rows in one launch whose
  * workgroups wait for one another; where they cannot all be on the device within
  * 20 ms (other work holds it), one of them does the panel, with the same results.
+ * Its exchange words are the end of the workspace (0.43 MB at n = 720); a buffer
+ * without room for them is accepted and takes two launches per column instead.
  * The HEMV of trailing blocks above 2048 rows reads only their lower half;
  * its partial sums take up to max(49, (n + 63) / 256) x n x 16 B more
  * workspace (n > 2049).
@@ -301,7 +303,8 @@ int32_t bse_dipole_weights(const bse_problem *p, const void *B, int32_t nblk,
  * in Hmu.  The workspace grows by about n^2 16 B (all reflectors of either
  * reduction) plus 400 K n B (inverse-iteration scratch) for K > 0.
  * Errors: n < 1 or n > 65536 (BSE_ESHAPE), NULL pointers or nrefine outside
- * 0 .. 256 (BSE_EINVAL), ws_bytes < bse_block_eigh_ws (BSE_EWORKSPACE).  The
+ * 0 .. 256 (BSE_EINVAL), ws_bytes < bse_block_eigh_ws, but for the exchange words
+ * (BSE_EWORKSPACE).  The
  * call only enqueues kernels; eigenvalues it could not refine (clusters of
  * more than 8 members) or non-finite results are reported afterwards by
  * bse_block_eigh_status (BSE_ENOCONV).
@@ -394,7 +397,9 @@ int32_t bse_block_eigh_noalloc(int64_t n, const void *Hmu, int64_t ld, int32_t h
  * block), run in lockstep: every launch advances every block that still has
  * columns left by one step, so the per-column launch latency is paid once
  * per column of the largest block instead of once per column of every block.
- *   bse_batch_eigh_ws      workspace bytes for blocks of sizes h_n[nb]
+ *   bse_batch_eigh_ws      workspace bytes for blocks of sizes h_n[nb] (FP64: with
+ *                          the exchange words of one-launch panels; a plan on a
+ *                          buffer without room for them does without)
  *   bse_batch_eigh_plan    validates the blocks, lays out the workspace, and
  *                          uploads the per-block descriptors and launch tables
  *                          (synchronises `stream`); returns a plan id in

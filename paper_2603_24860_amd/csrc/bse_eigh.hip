@@ -2507,11 +2507,13 @@ __global__ __launch_bounds__(ENT) void k_rq_fin(Desc D) {
 // ---------------------------------------------------------------------------
 // single block
 // ---------------------------------------------------------------------------
+// panels: the workspace holds the exchange words of k_panel
 template <typename TH, typename TA>
 int32_t eigh_run(int64_t n, const void *Hmu, int64_t ld, const void *Bmu, double *omega,
-                 double *pole, double *osc, void *ws, hipStream_t s, int64_t K) {
+                 double *pole, double *osc, void *ws, hipStream_t s, int64_t K, bool panels) {
   Desc D;
   ws_layout(n, sizeof(TA) == 8, &D, (char *)ws, K);
+  if (!panels) D.px = nullptr;
   D.H = Hmu;
   D.ld = ld;
   D.B = (const double2 *)Bmu;
@@ -2538,7 +2540,7 @@ int32_t eigh_run(int64_t n, const void *Hmu, int64_t ld, const void *Bmu, double
     }
     const int nbk = g_nbk(n, j0);
     if (K > 0) D.V = D0.Vall + j0 * D0.ldv;  // keep every reflector for the back-transform
-    const bool pan = g_pan(n, j0, sizeof(TA) == 8);
+    const bool pan = D.px && g_pan(n, j0, sizeof(TA) == 8);
     if constexpr (sizeof(TA) == 8) if (pan) {
       const size_t lds = size_t(n - j0) * sizeof(double2);
       const dim3 g((unsigned)g_pan_wgs(n - j0 - 1));
@@ -2718,6 +2720,7 @@ struct BatchLaunch {
 
 struct BatchPlan {
   int nb = 0, h_fp64 = 0, prec = 0, wpr = 4, htile = 0;
+  bool panels = false;  // the workspace holds the exchange words of k_panel
   char *ws = nullptr;
   Desc *d_desc = nullptr;
   int *d_pre = nullptr;
@@ -2731,6 +2734,7 @@ void plan_launches(BatchPlan &P, std::vector<int> &pre) {
   P.launches.clear();
   pre.clear();
   const int nb = P.nb;
+  auto pan = [&](int b, int64_t j0) { return P.panels && g_pan(P.n[b], j0, sizeof(TA) == 8); };
   auto add = [&](int kind, int64_t j, int cur) {
     BatchLaunch L{kind, j, cur, 0, 0, pre.size(), 0, 0};
     int64_t tot = 0;
@@ -2738,7 +2742,7 @@ void plan_launches(BatchPlan &P, std::vector<int> &pre) {
     for (int b = 0; b < nb; ++b) {
       // (the largest blocks' panels may still run column by column)
       const bool col = kind == K_COL0 || kind == K_COLA || kind == K_COLB;
-      const int64_t w = col && g_pan(P.n[b], j - j % NBK, sizeof(TA) == 8)
+      const int64_t w = col && pan(b, j - j % NBK)
                             ? 0 : kind_wgs<TA>(kind, P.n[b], j, P.wpr, P.htile);
       if (w == 0) break;  // sorted descending: the rest are inactive too
       tot += w;
@@ -2762,7 +2766,7 @@ void plan_launches(BatchPlan &P, std::vector<int> &pre) {
   // panels of one launch each: as many blocks per launch as PAN_BATCH workgroups
   // hold, all of one row count per workgroup
   auto panels = [&](int64_t j0) {
-    auto on = [&](int b) { return b < nb && g_pan(P.n[b], j0, sizeof(TA) == 8); };
+    auto on = [&](int b) { return b < nb && pan(b, j0); };
     int b = 0;
     while (b < nb && j0 < g_tail0(P.n[b]) && !on(b)) ++b;
     while (on(b)) {
@@ -2852,27 +2856,28 @@ std::mutex g_plan_mu;
 std::map<int64_t, BatchPlan> g_plans;
 int64_t g_next_plan = 1;
 
-size_t batch_ws_bytes(int32_t nb, const int64_t *h_n, bool a_fp64, std::vector<size_t> *offs,
-                      size_t *desc_off, size_t *pre_off, size_t pre_ints) {
+// upper bound of the prefix-table size: launches x (active blocks + 1)
+size_t pre_bound(int32_t nb, const int64_t *h_n, bool panels) {
+  int64_t nmax = 0;
+  for (int b = 0; b < nb; ++b) nmax = std::max(nmax, h_n[b]);
+  // 9 one-off kinds; the k_panel launches of one panel index hold at most 2 nb entries
+  const size_t launches = 9 + size_t(cdiv(nmax, NBK)) * (2 * NBK + 2 + (panels ? 2 : 0));
+  return launches * size_t(nb + 1);
+}
+
+// panels: with the exchange words of k_panel (FP64 storage), each block's at its end
+size_t batch_ws_bytes(int32_t nb, const int64_t *h_n, bool a_fp64, bool panels,
+                      std::vector<size_t> *offs, size_t *desc_off, size_t *pre_off) {
   size_t off = 0;
   for (int b = 0; b < nb; ++b) {
     if (offs) offs->push_back(off);
-    off += ws_layout(h_n[b], a_fp64, nullptr, nullptr);
+    off += ws_layout(h_n[b], a_fp64, nullptr, nullptr) - (panels ? 0 : g_pan_bytes(h_n[b], a_fp64));
   }
   if (desc_off) *desc_off = off;
   off += align256(size_t(nb) * sizeof(Desc));
   if (pre_off) *pre_off = off;
-  off += align256(pre_ints * sizeof(int));
+  off += align256(pre_bound(nb, h_n, panels) * sizeof(int));
   return off;
-}
-
-// upper bound of the prefix-table size: launches x (active blocks + 1)
-size_t pre_bound(int32_t nb, const int64_t *h_n) {
-  int64_t nmax = 0;
-  for (int b = 0; b < nb; ++b) nmax = std::max(nmax, h_n[b]);
-  // 9 one-off kinds; the k_panel launches of one panel index hold at most 2 nb entries
-  const size_t launches = 9 + size_t(cdiv(nmax, NBK)) * (2 * NBK + 2 + 2);
-  return launches * size_t(nb + 1);
 }
 
 }  // namespace bse
@@ -2904,9 +2909,12 @@ extern "C" int32_t bse_block_eigh(int64_t n, const void *Hmu, int64_t ld, int32_
     return fail(BSE_EINVAL, "nrefine = %d outside 0 .. %d", nrefine, KMAX);
   const int64_t K = std::min<int64_t>(nrefine, n);
   const bool two = takes_two_stage(n, K);
-  const size_t need = ws_layout(n, prec == BSE_FP64, nullptr, nullptr, K, two);
+  const bool a64 = prec == BSE_FP64;
+  const size_t full = ws_layout(n, a64, nullptr, nullptr, K, two);
+  const size_t need = full - (two ? 0 : g_pan_bytes(n, a64));  // the panels' words are last
   if (!ws || ws_bytes < need)
     return fail(BSE_EWORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
+  const bool pan = ws_bytes >= full;
   hipStream_t s = (hipStream_t)stream;
   if (two) {
     if (prec == BSE_FP64)
@@ -2916,10 +2924,10 @@ extern "C" int32_t bse_block_eigh(int64_t n, const void *Hmu, int64_t ld, int32_
                   : eigh_run_2s<float, float>(n, Hmu, ld, Bmu, omega, pole, osc, ws, s, K);
   }
   if (prec == BSE_FP64)
-    return h_fp64 ? eigh_run<double, double>(n, Hmu, ld, Bmu, omega, pole, osc, ws, s, K)
-                  : eigh_run<float, double>(n, Hmu, ld, Bmu, omega, pole, osc, ws, s, K);
-  return h_fp64 ? eigh_run<double, float>(n, Hmu, ld, Bmu, omega, pole, osc, ws, s, K)
-                : eigh_run<float, float>(n, Hmu, ld, Bmu, omega, pole, osc, ws, s, K);
+    return h_fp64 ? eigh_run<double, double>(n, Hmu, ld, Bmu, omega, pole, osc, ws, s, K, pan)
+                  : eigh_run<float, double>(n, Hmu, ld, Bmu, omega, pole, osc, ws, s, K, pan);
+  return h_fp64 ? eigh_run<double, float>(n, Hmu, ld, Bmu, omega, pole, osc, ws, s, K, pan)
+                : eigh_run<float, float>(n, Hmu, ld, Bmu, omega, pole, osc, ws, s, K, pan);
 }
 
 // ---------------------------------------------------------------------------
@@ -2977,7 +2985,7 @@ extern "C" int32_t bse_block_eigh_noalloc(int64_t n, const void *Hmu, int64_t ld
     return fail(BSE_EINVAL, "nrefine = %d outside 0 .. %d", nrefine, KMAX);
   const int64_t K = std::min<int64_t>(nrefine, n);
   const bool a64 = prec == BSE_FP64;
-  const size_t pan = g_pan_bytes(n, a64), need = ws_layout(n, prec == BSE_FP64, nullptr, nullptr, K) - pan;
+  const size_t pan = g_pan_bytes(n, a64), need = ws_layout(n, a64, nullptr, nullptr, K) - pan;
   if (need > SCRATCH_BYTES || pan > SCRATCH_PAN)
     return fail(BSE_EWORKSPACE,
                 "n = %lld needs %zu bytes of workspace; the static scratch holds %zu",
@@ -2987,10 +2995,10 @@ extern "C" int32_t bse_block_eigh_noalloc(int64_t n, const void *Hmu, int64_t ld
   const int32_t st = scratch_of(s, &ws);
   if (st != BSE_OK) return st;
   if (prec == BSE_FP64)
-    return h_fp64 ? eigh_run<double, double>(n, Hmu, ld, Bmu, omega, pole, osc, ws, s, K)
-                  : eigh_run<float, double>(n, Hmu, ld, Bmu, omega, pole, osc, ws, s, K);
-  return h_fp64 ? eigh_run<double, float>(n, Hmu, ld, Bmu, omega, pole, osc, ws, s, K)
-                : eigh_run<float, float>(n, Hmu, ld, Bmu, omega, pole, osc, ws, s, K);
+    return h_fp64 ? eigh_run<double, double>(n, Hmu, ld, Bmu, omega, pole, osc, ws, s, K, true)
+                  : eigh_run<float, double>(n, Hmu, ld, Bmu, omega, pole, osc, ws, s, K, true);
+  return h_fp64 ? eigh_run<double, float>(n, Hmu, ld, Bmu, omega, pole, osc, ws, s, K, true)
+                : eigh_run<float, float>(n, Hmu, ld, Bmu, omega, pole, osc, ws, s, K, true);
 }
 
 extern "C" int32_t bse_block_eigh_status(int64_t n, int32_t prec, int32_t nrefine,
@@ -3058,8 +3066,8 @@ extern "C" size_t bse_batch_eigh_ws(int32_t nb, const int64_t *h_n, int32_t h_fp
                                     int32_t prec) {
   (void)h_fp64;
   if (check_batch(nb, h_n, prec)) return 0;
-  return batch_ws_bytes(nb, h_n, prec == BSE_FP64, nullptr, nullptr, nullptr,
-                        pre_bound(nb, h_n));
+  const bool a64 = prec == BSE_FP64;
+  return batch_ws_bytes(nb, h_n, a64, a64, nullptr, nullptr, nullptr);
 }
 
 extern "C" int32_t bse_batch_eigh_plan(int32_t nb, const int64_t *h_n, const void *const *h_Hmu,
@@ -3086,11 +3094,12 @@ extern "C" int32_t bse_batch_eigh_plan(int32_t nb, const int64_t *h_n, const voi
   for (int b = 0; b < nb; ++b) ns[b] = h_n[order[b]];
   std::vector<size_t> offs;
   size_t desc_off = 0, pre_off = 0;
-  const size_t need = batch_ws_bytes(nb, ns.data(), a64, &offs, &desc_off, &pre_off,
-                                     pre_bound(nb, ns.data()));
+  const size_t need = batch_ws_bytes(nb, ns.data(), a64, false, nullptr, nullptr, nullptr);
   if (!ws || ws_bytes < need)
     return fail(BSE_EWORKSPACE, "workspace %zu < %zu bytes", ws_bytes, need);
   BatchPlan P;
+  P.panels = a64 && ws_bytes >= batch_ws_bytes(nb, ns.data(), a64, true, nullptr, nullptr, nullptr);
+  batch_ws_bytes(nb, ns.data(), a64, P.panels, &offs, &desc_off, &pre_off);
   P.nb = nb;
   P.h_fp64 = h_fp64 ? 1 : 0;
   P.prec = prec;
@@ -3103,6 +3112,7 @@ extern "C" int32_t bse_batch_eigh_plan(int32_t nb, const int64_t *h_n, const voi
   for (int b = 0; b < nb; ++b) {
     const int o = order[b];
     ws_layout(ns[b], a64, &D[b], P.ws + offs[b]);
+    if (!P.panels) D[b].px = nullptr;
     D[b].H = h_Hmu[o];
     D[b].ld = h_ld[o];
     D[b].B = (const double2 *)h_Bmu[o];
