@@ -347,8 +347,9 @@ int64_t bse_block_eigh_set_two_stage(int64_t nmin);
  *                (their omega is the unrefined FP64 bisection value): members
  *                of a degenerate cluster beyond its first 8, whose inverse
  *                iteration is not run, or a Rayleigh quotient that is not finite;
- *   h_status[1]  eigenvalues that are not finite (the tridiagonal step met a
- *                non-finite matrix; outputs undefined);
+ *   h_status[1]  eigenvalues that are not finite: all n (omega NaN) where the
+ *                tridiagonal matrix is not, because Hmu is not or because a
+ *                workgroup of the reduction waited in vain for another;
  *   h_status[2]  clusters that straddle the refinement bound K (their members
  *                below K are refined, their pole stays the unrefined centre);
  *   h_status[3]  0 (reserved).

@@ -1229,7 +1229,8 @@ __device__ __forceinline__ void b_her2k(int64_t n, int64_t c0, int nbk,
 // tridiagonal eigenvalues (multisection) and cluster weights
 // ---------------------------------------------------------------------------
 // scalars: [0] Gershgorin low, [1] high, [2] |T| (max row sum), [3] pivmin,
-// [4] cluster gap tolerance
+// [4] cluster gap tolerance.  A T that is not finite has no interval: [0] and [1] are NaN
+// (fmin and fmax would pass over its entries), and so is every eigenvalue.
 __device__ __forceinline__ void b_tri_prep(int64_t n, const double *__restrict__ d,
                                                   const double *__restrict__ e, double ctol_rel,
                                                   double *__restrict__ e2,
@@ -1237,12 +1238,14 @@ __device__ __forceinline__ void b_tri_prep(int64_t n, const double *__restrict__
                                                   int32_t *__restrict__ status) {
   if (threadIdx.x < 4) status[threadIdx.x] = 0;  // counters of this solve
   __shared__ double s_lo[RNT / 64], s_hi[RNT / 64], s_tn[RNT / 64];
+  bool bad = false;
   double lo = 1e300, hi = -1e300, tn = 0;
   for (int64_t k = threadIdx.x; k < n; k += RNT) {
     const double el = k > 0 ? fabs(e[k - 1]) : 0.0, er = k + 1 < n ? fabs(e[k]) : 0.0;
     lo = fmin(lo, d[k] - el - er);
     hi = fmax(hi, d[k] + el + er);
     tn = fmax(tn, fabs(d[k]) + el + er);
+    bad |= !(fabs(d[k]) < __builtin_inf() && er < __builtin_inf());
     if (k + 1 < n) e2[k] = e[k] * e[k];
   }
   for (int o = 32; o > 0; o >>= 1) {
@@ -1256,7 +1259,7 @@ __device__ __forceinline__ void b_tri_prep(int64_t n, const double *__restrict__
     s_hi[w] = hi;
     s_tn[w] = tn;
   }
-  __syncthreads();
+  bad = __syncthreads_or(bad);
   if (threadIdx.x == 0) {
     for (int i = 0; i < RNT / 64; ++i) {
       lo = fmin(lo, s_lo[i]);
@@ -1265,8 +1268,8 @@ __device__ __forceinline__ void b_tri_prep(int64_t n, const double *__restrict__
     }
     const double pivmin = 1e-100 * fmax(1.0, tn);
     const double pad = 4.4e-16 * fmax(1.0, tn) * double(n) + pivmin;
-    sc[0] = lo - pad;
-    sc[1] = hi + pad;
+    sc[0] = bad ? __builtin_nan("") : lo - pad;
+    sc[1] = bad ? __builtin_nan("") : hi + pad;
     sc[2] = tn;
     sc[3] = pivmin;
     sc[4] = ctol_rel * fmax(1.0, tn);
@@ -2504,6 +2507,9 @@ __global__ __launch_bounds__(ENT) void k_rq_fin(Desc D) {
 
 }  // namespace
 
+// Polls of a wait inside k_sb_chase, for the solves of this host thread.
+thread_local int32_t t_chase_polls = CHASE_SPIN;
+
 // ---------------------------------------------------------------------------
 // single block
 // ---------------------------------------------------------------------------
@@ -2620,6 +2626,7 @@ int32_t eigh_run_2s(int64_t n, const void *Hmu, int64_t ld, const void *Bmu, dou
                     double *pole, double *osc, void *ws, hipStream_t s, int64_t K) {
   Desc D;
   ws_layout(n, sizeof(TA) == 8, &D, (char *)ws, K, true);
+  D.chase_polls = t_chase_polls;
   D.H = Hmu;
   D.ld = ld;
   D.B = (const double2 *)Bmu;
@@ -2883,6 +2890,10 @@ size_t batch_ws_bytes(int32_t nb, const int64_t *h_n, bool a_fp64, bool panels,
 }  // namespace bse
 
 using namespace bse;
+
+extern "C" void bse_eigh_limits(int32_t chase_polls) {
+  t_chase_polls = chase_polls < 0 ? CHASE_SPIN : chase_polls;
+}
 
 extern "C" size_t bse_block_eigh_ws(int64_t n, int32_t h_fp64, int32_t prec, int32_t nrefine) {
   (void)h_fp64;

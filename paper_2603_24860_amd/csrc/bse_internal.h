@@ -77,6 +77,11 @@ int32_t seed_pieces(int64_t plan, SeedPieces *out);
 
 }  // namespace bse
 
+// For the tests of what the eigensolver does when a wait runs out; not part of the
+// interface.  Polls of one wait inside k_sb_chase, for the solves that this host thread
+// enqueues from now on; negative: the default.
+extern "C" void bse_eigh_limits(int32_t chase_polls);
+
 #define BSE_HIP_CHECK(expr)                                                        \
   do {                                                                             \
     hipError_t e_ = (expr);                                                        \

@@ -821,7 +821,10 @@ constexpr int BCU = SBW * SBW / BCT;  // entries per thread and block
 constexpr int BCG = BCT / SBW;        // row groups g (q = g + BCG u)
 // KEEP (refinement): every reflector is also stored for the back-transformation
 constexpr int CHASE_WGS = 256;       // workgroups of the chase, at most
-constexpr int CHASE_SPIN = 1 << 26;  // polls of one wait (a minute; never reached)
+// Polls of one wait (a minute).  A wait ends by itself unless the device is broken;
+// should one run out, the workgroup leaves NaN in the subdiagonal entries of its sweeps,
+// which k_tri_prep turns into a solve without finite eigenvalues, and waits no more.
+constexpr int CHASE_SPIN = 1 << 26;
 __device__ __forceinline__ double2 band_ld(const double2 *p) {
   const double *q = reinterpret_cast<const double *>(p);
   return double2{__hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
@@ -844,6 +847,8 @@ __global__ __launch_bounds__(BCT) void k_sb_chase(Desc D) {
   __shared__ double2 us[SBW];           // the reflector of the previous task
   __shared__ double xsum;
   __shared__ int sweep_s, done_s;
+  __shared__ int polls_s;  // polls of a wait, -1 once one ran out (in LDS, so that the loop
+                           // over the tasks stays one of scalar branches)
   const int n = (int)D.n;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, p = tid % SBW, g = tid / SBW;
   double2 *band = D.band;
@@ -857,7 +862,10 @@ __global__ __launch_bounds__(BCT) void k_sb_chase(Desc D) {
   auto ticket = [&]() {
     return __hip_atomic_fetch_add(chase_next(D), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
-  if (tid == 0) sweep_s = ticket();
+  if (tid == 0) {
+    sweep_s = ticket();
+    polls_s = D.chase_polls;
+  }
   __syncthreads();
   // A pass of either loop begins and ends at a barrier of the workgroup or the wave:
   // where it ends in a branch of thread 0 and the next begins with one, the compiler
@@ -885,8 +893,11 @@ __global__ __launch_bounds__(BCT) void k_sb_chase(Desc D) {
           if (tid == 0) publish(i, k);
           owed = false;
         }
-        if (tid == 0)
-          for (int s = 0; s < CHASE_SPIN && ahead() < want; ++s) __builtin_amdgcn_s_sleep(1);
+        if (tid == 0) {
+          const int polls = polls_s;
+          for (int s = 0; s < polls && ahead() < want; ++s) __builtin_amdgcn_s_sleep(1);
+          if (ahead() < want) polls_s = -1;
+        }
         __syncthreads();
       }
       // ---- loads, all issued together from in-bounds addresses ----
@@ -1025,6 +1036,7 @@ __global__ __launch_bounds__(BCT) void k_sb_chase(Desc D) {
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (tid == 0) {
+      if (polls_s < 0) D.e[i] = __builtin_nan("");
       publish(i, kmax + 1);
       sweep_s = ticket();
     }

@@ -110,6 +110,7 @@ struct Desc {
   double2 *rfl;              // [n][SBW] its first word: finished tasks of a bulge-chasing sweep
   double2 *rtau;             // [n] its first word: the next sweep that no workgroup has taken
   double2 *sink;             // [SINK] target of the stores of masked lanes (never read)
+  int32_t chase_polls;       // polls of one wait of k_sb_chase, at most
   // two-stage reduction with refinement (K > 0): every reflector of both
   // stages, for the back-transformation; null otherwise
   double2 *rall;             // chase, packed: sweep i at g_bc_off(n, i), rows i + 1 .. n - 1;

@@ -43,7 +43,10 @@
 typedef unsigned long long u64;
 constexpr u64 XNONE = 0x7ff1dead5eed5eedull;
 constexpr long long PAN_WAIT = 2000000;  // 20 ms of the 100 MHz clock
-constexpr int PAN_SPIN = 1 << 22;        // polls of a committed panel (seconds; never reached)
+// Polls of a committed panel (seconds).  Its waits end by themselves unless the device
+// is broken; a word that never came is a NaN in every later column and so in the
+// tridiagonal, where k_tri_prep turns it into a solve without finite eigenvalues.
+constexpr int PAN_SPIN = 1 << 22;
 
 __device__ __forceinline__ u64 xld(const u64 *p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -57,15 +60,6 @@ __device__ __forceinline__ void xput(u64 *p, double2 v) {  // complex entry: two
 }
 __device__ __forceinline__ double2 xval(u64 a, u64 b) {
   return double2{__longlong_as_double((long long)a), __longlong_as_double((long long)b)};
-}
-// the complex entry at p, waited for
-__device__ __forceinline__ double2 xget(const u64 *p) {
-  u64 a = xld(p), b = xld(p + 1);
-  for (int k = 0; (a == XNONE || b == XNONE) && k < PAN_SPIN; ++k) {
-    a = xld(p);
-    b = xld(p + 1);
-  }
-  return xval(a, b);
 }
 __device__ __forceinline__ void wait_stores() { __builtin_amdgcn_s_waitcnt(0); }
 
