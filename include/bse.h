@@ -284,8 +284,10 @@ int32_t bse_dipole_weights(const bse_problem *p, const void *B, int32_t nblk,
  * prec: FP64 (all FP64), FP32 (FP32 storage of the working copy, its HEMV
  * and trailing updates; FP64 panel vectors, scalars and tridiagonal step).
  * FP64 storage reduces each panel of up to 2304 trailing rows in one launch whose
- * workgroups wait for one another; where they cannot all be on the device within
- * 20 ms (other work holds it), one of them does the panel, with the same results.
+ * workgroups wait for one another, where they take at most a quarter of those that
+ * the device (of a stream with a compute-unit mask: its units) holds at a time, else
+ * in two launches per column.  Where they cannot all be on the device within 20 ms
+ * (other work holds it), one of them does the panel, with the same results.
  * Its exchange words are the end of the workspace (0.43 MB at n = 720); a buffer
  * without room for them is accepted and takes two launches per column instead.
  * The HEMV of trailing blocks above 2048 rows reads only their lower half;
@@ -304,9 +306,8 @@ int32_t bse_dipole_weights(const bse_problem *p, const void *B, int32_t nblk,
  * reduction) plus 400 K n B (inverse-iteration scratch) for K > 0.
  * Errors: n < 1 or n > 65536 (BSE_ESHAPE), NULL pointers or nrefine outside
  * 0 .. 256 (BSE_EINVAL), ws_bytes < bse_block_eigh_ws, but for the exchange words
- * (BSE_EWORKSPACE).  The
- * call only enqueues kernels; eigenvalues it could not refine (clusters of
- * more than 8 members) or non-finite results are reported afterwards by
+ * (BSE_EWORKSPACE).  The call only enqueues kernels; eigenvalues it could not refine
+ * (clusters of more than 8 members) or non-finite results are reported afterwards by
  * bse_block_eigh_status (BSE_ENOCONV).
  * ------------------------------------------------------------------------- */
 size_t bse_block_eigh_ws(int64_t n, int32_t h_fp64, int32_t prec, int32_t nrefine);
@@ -400,7 +401,9 @@ int32_t bse_block_eigh_noalloc(int64_t n, const void *Hmu, int64_t ld, int32_t h
  * per column of the largest block instead of once per column of every block.
  *   bse_batch_eigh_ws      workspace bytes for blocks of sizes h_n[nb] (FP64: with
  *                          the exchange words of one-launch panels; a plan on a
- *                          buffer without room for them does without)
+ *                          buffer without room for them does without).  The
+ *                          one-launch panels are laid out for the device, and the
+ *                          compute units of the stream, that the plan is made on
  *   bse_batch_eigh_plan    validates the blocks, lays out the workspace, and
  *                          uploads the per-block descriptors and launch tables
  *                          (synchronises `stream`); returns a plan id in

@@ -2509,6 +2509,39 @@ __global__ __launch_bounds__(ENT) void k_rq_fin(Desc D) {
 
 // Polls of a wait inside k_sb_chase, for the solves of this host thread.
 thread_local int32_t t_chase_polls = CHASE_SPIN;
+// Workgroups of k_panel that the device holds, for the solves and plans of this host
+// thread; negative: asked for.
+thread_local int64_t t_pan_slots = -1;
+
+// Workgroups of k_panel (the largest) that the compute units of stream s hold at a time.
+// Two properties of the device, looked up once, and the stream's compute-unit mask.
+int32_t panel_slots(hipStream_t s, int64_t *slots) {
+  constexpr int MAXDEV = 64;
+  static std::atomic<int> s_ncu[MAXDEV], s_per[MAXDEV];
+  if (t_pan_slots >= 0) {
+    *slots = t_pan_slots;
+    return BSE_OK;
+  }
+  int dev = -1;
+  BSE_HIP_CHECK(hipGetDevice(&dev));
+  if (dev < 0 || dev >= MAXDEV) return fail(BSE_EDEVICE, "device %d out of range", dev);
+  int ncu = s_ncu[dev].load(), per = s_per[dev].load();
+  if (ncu == 0 || per == 0) {
+    BSE_HIP_CHECK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
+    BSE_HIP_CHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_panel<3>, ENT,
+                                                               (PAN_M + 1) * sizeof(double2)));
+    s_ncu[dev].store(ncu);
+    s_per[dev].store(per);
+  }
+  uint32_t mask[32];
+  int on = 0;
+  if (hipExtStreamGetCUMask(s, 32, mask) == hipSuccess)
+    for (int i = 0; i < std::min(32, (ncu + 31) / 32); ++i) on += __builtin_popcount(mask[i]);
+  else
+    (void)hipGetLastError();
+  *slots = int64_t(on > 0 ? std::min(on, ncu) : ncu) * per;
+  return BSE_OK;
+}
 
 // ---------------------------------------------------------------------------
 // single block
@@ -2519,7 +2552,14 @@ int32_t eigh_run(int64_t n, const void *Hmu, int64_t ld, const void *Bmu, double
                  double *pole, double *osc, void *ws, hipStream_t s, int64_t K, bool panels) {
   Desc D;
   ws_layout(n, sizeof(TA) == 8, &D, (char *)ws, K);
-  if (!panels) D.px = nullptr;
+  int pan_limit = 0;  // workgroups of a single-launch panel, at most
+  if (panels && sizeof(TA) == 8 && D.px) {
+    int64_t slots = 0;
+    const int32_t st = panel_slots(s, &slots);
+    if (st) return st;
+    pan_limit = g_pan_limit(slots);
+  }
+  if (pan_limit < 1) D.px = nullptr;
   D.H = Hmu;
   D.ld = ld;
   D.B = (const double2 *)Bmu;
@@ -2546,7 +2586,7 @@ int32_t eigh_run(int64_t n, const void *Hmu, int64_t ld, const void *Bmu, double
     }
     const int nbk = g_nbk(n, j0);
     if (K > 0) D.V = D0.Vall + j0 * D0.ldv;  // keep every reflector for the back-transform
-    const bool pan = D.px && g_pan(n, j0, sizeof(TA) == 8);
+    const bool pan = D.px && g_pan(n, j0, sizeof(TA) == 8) && g_pan_wgs(n - j0 - 1) <= pan_limit;
     if constexpr (sizeof(TA) == 8) if (pan) {
       const size_t lds = size_t(n - j0) * sizeof(double2);
       const dim3 g((unsigned)g_pan_wgs(n - j0 - 1));
@@ -2710,10 +2750,6 @@ inline bool takes_two_stage(int64_t n, int64_t) { return n >= g_two_stage_min.lo
 // ---------------------------------------------------------------------------
 // batched: every active block advances one step per launch
 // ---------------------------------------------------------------------------
-// workgroups of one batched k_panel launch, at most (a third of a compute unit
-// each: one batch and one single panel fit on the device side by side)
-constexpr int PAN_BATCH = 512;
-
 struct BatchLaunch {
   int kind;
   int64_t j;
@@ -2728,6 +2764,7 @@ struct BatchLaunch {
 struct BatchPlan {
   int nb = 0, h_fp64 = 0, prec = 0, wpr = 4, htile = 0;
   bool panels = false;  // the workspace holds the exchange words of k_panel
+  int pan_limit = 0, pan_batch = 0;  // workgroups of one panel, of a k_panel launch, at most
   char *ws = nullptr;
   Desc *d_desc = nullptr;
   int *d_pre = nullptr;
@@ -2741,7 +2778,10 @@ void plan_launches(BatchPlan &P, std::vector<int> &pre) {
   P.launches.clear();
   pre.clear();
   const int nb = P.nb;
-  auto pan = [&](int b, int64_t j0) { return P.panels && g_pan(P.n[b], j0, sizeof(TA) == 8); };
+  auto pan = [&](int b, int64_t j0) {
+    return P.panels && g_pan(P.n[b], j0, sizeof(TA) == 8) &&
+           g_pan_wgs(P.n[b] - j0 - 1) <= P.pan_limit;
+  };
   auto add = [&](int kind, int64_t j, int cur) {
     BatchLaunch L{kind, j, cur, 0, 0, pre.size(), 0, 0};
     int64_t tot = 0;
@@ -2770,7 +2810,7 @@ void plan_launches(BatchPlan &P, std::vector<int> &pre) {
   add(K_W0, 0, 0);
   add(K_RANK2, 0, 0);
   int cur = 0;
-  // panels of one launch each: as many blocks per launch as PAN_BATCH workgroups
+  // panels of one launch each: as many blocks per launch as pan_batch workgroups
   // hold, all of one row count per workgroup
   auto panels = [&](int64_t j0) {
     auto on = [&](int b) { return b < nb && pan(b, j0); };
@@ -2782,7 +2822,7 @@ void plan_launches(BatchPlan &P, std::vector<int> &pre) {
       pre.push_back(0);
       for (; on(b) && g_pan_wr(P.n[b] - j0 - 1) == L.cur; ++b) {
         const int w = g_pan_wgs(P.n[b] - j0 - 1);
-        if (L.nact > 0 && L.total + w > PAN_BATCH) break;
+        if (L.nact > 0 && L.total + w > P.pan_batch) break;
         L.total += w;
         pre.push_back(L.total);
         ++L.nact;
@@ -2894,6 +2934,8 @@ using namespace bse;
 extern "C" void bse_eigh_limits(int32_t chase_polls) {
   t_chase_polls = chase_polls < 0 ? CHASE_SPIN : chase_polls;
 }
+
+extern "C" void bse_eigh_panel_slots(int64_t slots) { t_pan_slots = slots; }
 
 extern "C" size_t bse_block_eigh_ws(int64_t n, int32_t h_fp64, int32_t prec, int32_t nrefine) {
   (void)h_fp64;
@@ -3111,6 +3153,13 @@ extern "C" int32_t bse_batch_eigh_plan(int32_t nb, const int64_t *h_n, const voi
   BatchPlan P;
   P.panels = a64 && ws_bytes >= batch_ws_bytes(nb, ns.data(), a64, true, nullptr, nullptr, nullptr);
   batch_ws_bytes(nb, ns.data(), a64, P.panels, &offs, &desc_off, &pre_off);
+  if (P.panels) {
+    int64_t slots = 0;
+    st = panel_slots((hipStream_t)stream, &slots);
+    if (st) return st;
+    P.pan_limit = g_pan_limit(slots);
+    P.pan_batch = g_pan_batch(slots);
+  }
   P.nb = nb;
   P.h_fp64 = h_fp64 ? 1 : 0;
   P.prec = prec;
@@ -3123,7 +3172,7 @@ extern "C" int32_t bse_batch_eigh_plan(int32_t nb, const int64_t *h_n, const voi
   for (int b = 0; b < nb; ++b) {
     const int o = order[b];
     ws_layout(ns[b], a64, &D[b], P.ws + offs[b]);
-    if (!P.panels) D[b].px = nullptr;
+    if (P.pan_limit < 1) D[b].px = nullptr;
     D[b].H = h_Hmu[o];
     D[b].ld = h_ld[o];
     D[b].B = (const double2 *)h_Bmu[o];

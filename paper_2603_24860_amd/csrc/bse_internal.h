@@ -81,6 +81,9 @@ int32_t seed_pieces(int64_t plan, SeedPieces *out);
 // interface.  Polls of one wait inside k_sb_chase, for the solves that this host thread
 // enqueues from now on; negative: the default.
 extern "C" void bse_eigh_limits(int32_t chase_polls);
+// For the tests of small devices; likewise.  Workgroups of k_panel that the device is
+// taken to hold at a time; negative: the device is asked.
+extern "C" void bse_eigh_panel_slots(int64_t slots);
 
 #define BSE_HIP_CHECK(expr)                                                        \
   do {                                                                             \

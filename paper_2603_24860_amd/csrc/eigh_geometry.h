@@ -217,8 +217,15 @@ __host__ __device__ __forceinline__ int64_t g_yslots(int64_t n) {
 // are kept as they are, at 33 ms where the panels took 24 (n = 2160).
 // k_panel:
 // g_pan_rows(m) rows per workgroup, a multiple of its four waves, so that at most
-// PAN_WGS workgroups share a panel.
+// PAN_WGS workgroups share a panel.  They wait for one another, so a panel is taken
+// in one launch only where it asks for a quarter of the workgroups that the device
+// holds at a time (g_pan_limit), as many as there are hardware queues: 192 of
+// 768 on a whole MI355X, 24 (192 rows) on a partition of 32 compute units, where the
+// panels of n = 720 would wait 20 ms each and then run in one workgroup.  A launch
+// of a batch takes up to two thirds (g_pan_batch): it fits beside a single panel.
 constexpr int PAN_WGS = 192;
+inline int g_pan_limit(int64_t slots) { return (int)std::min<int64_t>(PAN_WGS, slots / 4); }
+inline int g_pan_batch(int64_t slots) { return (int)(slots * 2 / 3); }
 constexpr int64_t PAN_M = 12 * PAN_WGS;
 __host__ __device__ __forceinline__ int g_pan_wr(int64_t m) { return m <= 8 * PAN_WGS ? 2 : 3; }
 __host__ __device__ __forceinline__ int g_pan_rows(int64_t m) { return 4 * g_pan_wr(m); }

@@ -27,7 +27,8 @@
 //     all leave but workgroup 0, which runs every workgroup's part in turn (the
 //     same code and sums, so the same bits).  A launch holds at most PAN_WGS
 //     workgroups, three of which fit a compute unit: four launches fit side by
-//     side on the device.
+//     side on the device, and a device that holds fewer takes smaller panels
+//     (g_pan_limit).
 // Measured (one box, before -> now, us per column all in): n = 720 12.4 -> 6.6 (solve
 // 8.73 -> 5.28 ms), n = 162 (solve with build and spectra 1.57 -> 1.07 ms), n = 1500 (solve
 // 22.2 -> 14.1 ms).  Of the 16000 cycles of a column at n = 720 the two exchanges take
