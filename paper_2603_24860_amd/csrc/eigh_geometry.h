@@ -93,6 +93,7 @@ struct Desc {
   double *wref;              // [K] refined eigenvalues
   double2 *Tm;               // [cdiv(n - 1, NBK)][NBK][NBK] block-reflector factors T
   unsigned long long *px;    // exchange words of k_panel: entry counters, then four ring slots
+  int64_t pan_wait;          // clock ticks that a panel's workgroups wait for all of them
   int32_t *clo;              // [n] first index of each eigenvalue's cluster in the weights
   // two-stage reduction (full -> band of width SBW -> tridiagonal); null
   // unless the block takes that path
