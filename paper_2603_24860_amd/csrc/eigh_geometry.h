@@ -228,6 +228,7 @@ constexpr int PAN_WGS = 192;
 inline int g_pan_limit(int64_t slots) { return (int)std::min<int64_t>(PAN_WGS, slots / 4); }
 inline int g_pan_batch(int64_t slots) { return (int)(slots * 2 / 3); }
 constexpr int64_t PAN_M = 12 * PAN_WGS;
+constexpr int PAN_RING = 4;  // ring slots, see k_panel
 __host__ __device__ __forceinline__ int g_pan_wr(int64_t m) { return m <= 8 * PAN_WGS ? 2 : 3; }
 __host__ __device__ __forceinline__ int g_pan_rows(int64_t m) { return 4 * g_pan_wr(m); }
 __host__ __device__ __forceinline__ int g_pan_wgs(int64_t m) {
@@ -243,11 +244,24 @@ __host__ __device__ __forceinline__ int64_t g_pan_gmax(int64_t n) {
 // records (2 NBK per workgroup), the sums of y^dag v, the panel dot products, the
 // head row and y[m0], all complex
 __host__ __device__ __forceinline__ int64_t g_pan_ctrl(int64_t n) { return cdiv(n, NBK); }
-__host__ __device__ __forceinline__ int64_t g_pan_ring(int64_t n) {
-  return 2 * (n + (2 * NBK + 1) * g_pan_gmax(n) + 4 * NBK + 1);
+// where they start in a slot, in words
+struct PanOff {
+  int64_t col, rec, pa, bred, head, yj, end;
+};
+__host__ __device__ __forceinline__ PanOff g_pan_off(int64_t n) {
+  PanOff o;
+  o.col = 0;
+  o.rec = 2 * n;
+  o.pa = o.rec + 2 * int64_t(2 * NBK) * g_pan_gmax(n);
+  o.bred = o.pa + 2 * g_pan_gmax(n);
+  o.head = o.bred + 4 * NBK;
+  o.yj = o.head + 4 * NBK;
+  o.end = o.yj + 2;
+  return o;
 }
+__host__ __device__ __forceinline__ int64_t g_pan_ring(int64_t n) { return g_pan_off(n).end; }
 __host__ __device__ __forceinline__ int64_t g_pan_words(int64_t n) {
-  return 2 * g_pan_ctrl(n) + 4 * g_pan_ring(n);
+  return 2 * g_pan_ctrl(n) + PAN_RING * g_pan_ring(n);
 }
 
 // two-stage geometry: workgroups of the panel kernels over m panel rows

@@ -68,18 +68,12 @@ __device__ __forceinline__ void wait_stores() { __builtin_amdgcn_s_waitcnt(0); }
 
 // The exchange buffers of a block, carved from D.px (words); entries are complex.
 struct PanX {
-  u64 *col, *rec, *pa, *bred, *head, *yj;  // one ring slot each, see slot()
+  u64 *col, *rec, *pa, *bred, *head, *yj;  // one ring slot each, see pan_slot
 };
 __device__ __forceinline__ PanX pan_slot(u64 *px, int64_t n, int ring) {
-  PanX X;
-  u64 *p = px + 2 * g_pan_ctrl(n) + ring * g_pan_ring(n);
-  X.col = p;
-  X.rec = p + 2 * n;
-  X.pa = X.rec + 2 * int64_t(2 * NBK) * g_pan_gmax(n);
-  X.bred = X.pa + 2 * g_pan_gmax(n);
-  X.head = X.bred + 4 * NBK;
-  X.yj = X.head + 4 * NBK;
-  return X;
+  const PanOff o = g_pan_off(n);
+  u64 *p = px + 2 * g_pan_ctrl(n) + ring * o.end;
+  return PanX{p + o.col, p + o.rec, p + o.pa, p + o.bred, p + o.head, p + o.yj};
 }
 
 // Every ring word to XNONE and (ctrl) the entry counters to zero, shared by the
@@ -139,7 +133,7 @@ __device__ __forceinline__ void b_panel(const Desc &D, int j0, int g0) {
   const int gb = solo ? 0 : g0, ge = solo ? G : g0 + 1;
   for (int i = 0; i < NBK; ++i) {
     const int jn = j0 + i, m0 = jn + 1;
-    const PanX X = pan_slot(px, n, i & 3), XN = pan_slot(px, n, (i + 1) & 3);
+    const PanX X = pan_slot(px, n, i % PAN_RING), XN = pan_slot(px, n, (i + 1) % PAN_RING);
     double2 tau = {0, 0}, sc = {0, 0};
     // ================= A =================
     for (int g = gb; g < ge; ++g) {
@@ -433,7 +427,7 @@ __device__ __forceinline__ void b_panel(const Desc &D, int j0, int g0) {
       }
       // ---- every workgroup has finished column i - 1: its words back to XNONE ----
       if (i > 0) {
-        const PanX XP = pan_slot(px, n, (i + 3) & 3);
+        const PanX XP = pan_slot(px, n, (i - 1) % PAN_RING);
         const int t = tid - ENT / 2;
         if (t >= 0) {
           if (t < 2 * nr) xst(XP.col + 2 * rb + t, XNONE);
