@@ -288,7 +288,7 @@ int32_t bse_dipole_weights(const bse_problem *p, const void *B, int32_t nblk,
  * the device (of a stream with a compute-unit mask: its units) holds at a time, else
  * in two launches per column.  Where they cannot all be on the device within 20 ms
  * (other work holds it), one of them does the panel, with the same results but far
- * slower (every panel of n = 720 given up: 235 ms instead of 5.4).
+ * slower (every panel of n = 720 given up: 634 ms instead of 5.4).
  * Its exchange words are the end of the workspace (0.43 MB at n = 720); a buffer
  * without room for them is accepted and takes two launches per column instead.
  * The HEMV of trailing blocks above 2048 rows reads only their lower half;

@@ -2512,8 +2512,8 @@ thread_local int32_t t_chase_polls = CHASE_SPIN;
 // Workgroups of k_panel that the device holds, for the solves and plans of this host
 // thread; negative: asked for.
 thread_local int64_t t_pan_slots = -1;
-// Ticks that the workgroups of a panel wait for one another at its entry, likewise.
-thread_local int64_t t_pan_wait = PAN_WAIT;
+// Workgroups of each panel that are taken never to arrive, likewise.
+thread_local int32_t t_pan_absent = 0;
 
 // Workgroups of k_panel (the largest) that the compute units of stream s hold at a time.
 // Two properties of the device, looked up once, and the stream's compute-unit mask.
@@ -2562,7 +2562,7 @@ int32_t eigh_run(int64_t n, const void *Hmu, int64_t ld, const void *Bmu, double
     pan_limit = g_pan_limit(slots);
   }
   if (pan_limit < 1) D.px = nullptr;
-  D.pan_wait = t_pan_wait;
+  D.pan_absent = t_pan_absent;
   D.H = Hmu;
   D.ld = ld;
   D.B = (const double2 *)Bmu;
@@ -2939,7 +2939,7 @@ extern "C" void bse_eigh_limits(int32_t chase_polls) {
 }
 
 extern "C" void bse_eigh_panel_slots(int64_t slots) { t_pan_slots = slots; }
-extern "C" void bse_eigh_panel_wait(int64_t ticks) { t_pan_wait = ticks < 0 ? PAN_WAIT : ticks; }
+extern "C" void bse_eigh_panel_absent(int32_t wgs) { t_pan_absent = std::max(wgs, 0); }
 
 extern "C" size_t bse_block_eigh_ws(int64_t n, int32_t h_fp64, int32_t prec, int32_t nrefine) {
   (void)h_fp64;
@@ -3177,7 +3177,7 @@ extern "C" int32_t bse_batch_eigh_plan(int32_t nb, const int64_t *h_n, const voi
     const int o = order[b];
     ws_layout(ns[b], a64, &D[b], P.ws + offs[b]);
     if (P.pan_limit < 1) D[b].px = nullptr;
-    D[b].pan_wait = t_pan_wait;
+    D[b].pan_absent = t_pan_absent;
     D[b].H = h_Hmu[o];
     D[b].ld = h_ld[o];
     D[b].B = (const double2 *)h_Bmu[o];

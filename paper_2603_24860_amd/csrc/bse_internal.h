@@ -84,9 +84,9 @@ extern "C" void bse_eigh_limits(int32_t chase_polls);
 // For the tests of small devices; likewise.  Workgroups of k_panel that the device is
 // taken to hold at a time; negative: the device is asked.
 extern "C" void bse_eigh_panel_slots(int64_t slots);
-// For the tests of panels that are given up; likewise.  Ticks (10 ns) that the workgroups
-// of a panel wait for one another; 0: every panel is given up; negative: the default.
-extern "C" void bse_eigh_panel_wait(int64_t ticks);
+// For the tests of panels that are given up; likewise.  Workgroups of each panel that are
+// taken never to arrive (0: all do).
+extern "C" void bse_eigh_panel_absent(int32_t wgs);
 
 #define BSE_HIP_CHECK(expr)                                                        \
   do {                                                                             \

@@ -93,7 +93,6 @@ struct Desc {
   double *wref;              // [K] refined eigenvalues
   double2 *Tm;               // [cdiv(n - 1, NBK)][NBK][NBK] block-reflector factors T
   unsigned long long *px;    // exchange words of k_panel: entry counters, then four ring slots
-  int64_t pan_wait;          // clock ticks that a panel's workgroups wait for all of them
   int32_t *clo;              // [n] first index of each eigenvalue's cluster in the weights
   // two-stage reduction (full -> band of width SBW -> tridiagonal); null
   // unless the block takes that path
@@ -112,6 +111,7 @@ struct Desc {
   double2 *rtau;             // [n] its first word: the next sweep that no workgroup has taken
   double2 *sink;             // [SINK] target of the stores of masked lanes (never read)
   int32_t chase_polls;       // polls of one wait of k_sb_chase, at most
+  int32_t pan_absent;        // workgroups of each panel that are taken never to arrive
   // two-stage reduction with refinement (K > 0): every reflector of both
   // stages, for the back-transformation; null otherwise
   double2 *rall;             // chase, packed: sweep i at g_bc_off(n, i), rows i + 1 .. n - 1;
@@ -228,7 +228,7 @@ constexpr int PAN_WGS = 192;
 inline int g_pan_limit(int64_t slots) { return (int)std::min<int64_t>(PAN_WGS, slots / 4); }
 inline int g_pan_batch(int64_t slots) { return (int)(slots * 2 / 3); }
 constexpr int64_t PAN_M = 12 * PAN_WGS;
-constexpr int PAN_RING = 4;  // ring slots, see k_panel
+constexpr int PAN_RING = 4;  // ring slots, see k_panel (a power of two)
 __host__ __device__ __forceinline__ int g_pan_wr(int64_t m) { return m <= 8 * PAN_WGS ? 2 : 3; }
 __host__ __device__ __forceinline__ int g_pan_rows(int64_t m) { return 4 * g_pan_wr(m); }
 __host__ __device__ __forceinline__ int g_pan_wgs(int64_t m) {
@@ -244,14 +244,14 @@ __host__ __device__ __forceinline__ int64_t g_pan_gmax(int64_t n) {
 // records (2 NBK per workgroup), the sums of y^dag v, the panel dot products, the
 // head row and y[m0], all complex
 __host__ __device__ __forceinline__ int64_t g_pan_ctrl(int64_t n) { return cdiv(n, NBK); }
-// where they start in a slot, in words
-struct PanOff {
-  int64_t col, rec, pa, bred, head, yj, end;
+// where they start in the slot at p (P: a word's address, or its number in the slot)
+template <typename P> struct PanParts {
+  P col, rec, pa, bred, head, yj, end;
 };
-__host__ __device__ __forceinline__ PanOff g_pan_off(int64_t n) {
-  PanOff o;
-  o.col = 0;
-  o.rec = 2 * n;
+template <typename P> __host__ __device__ __forceinline__ PanParts<P> g_pan_parts(P p, int64_t n) {
+  PanParts<P> o;
+  o.col = p;
+  o.rec = p + 2 * n;
   o.pa = o.rec + 2 * int64_t(2 * NBK) * g_pan_gmax(n);
   o.bred = o.pa + 2 * g_pan_gmax(n);
   o.head = o.bred + 4 * NBK;
@@ -259,7 +259,9 @@ __host__ __device__ __forceinline__ PanOff g_pan_off(int64_t n) {
   o.end = o.yj + 2;
   return o;
 }
-__host__ __device__ __forceinline__ int64_t g_pan_ring(int64_t n) { return g_pan_off(n).end; }
+__host__ __device__ __forceinline__ int64_t g_pan_ring(int64_t n) {
+  return 2 * (n + (2 * NBK + 1) * g_pan_gmax(n) + 4 * NBK + 1);
+}
 __host__ __device__ __forceinline__ int64_t g_pan_words(int64_t n) {
   return 2 * g_pan_ctrl(n) + PAN_RING * g_pan_ring(n);
 }

@@ -26,8 +26,8 @@
 //     way), the panel is given up as a joint effort before any data was written:
 //     all leave but workgroup 0, which runs every workgroup's part in turn (the
 //     same code and sums, so the same bits; a solve whose every panel is given up
-//     takes 9.7 ms instead of 1.0 at n = 162, 235 instead of 5.4 at 720, 3.2 s
-//     instead of 30 ms at 2300, and the wait).  A launch holds at most PAN_WGS
+//     takes 70 ms instead of 1.0 at n = 162, 634 instead of 5.4 at 720, 4.6 s
+//     instead of 30 ms at 2300, of which 20 ms a panel are the wait).  A launch holds at most PAN_WGS
 //     workgroups, three of which fit a compute unit: four launches fit side by
 //     side on the device, and a device that holds fewer takes smaller panels
 //     (g_pan_limit).
@@ -45,7 +45,7 @@
 
 typedef unsigned long long u64;
 constexpr u64 XNONE = 0x7ff1dead5eed5eedull;
-constexpr int64_t PAN_WAIT = 2000000;  // 20 ms of the 100 MHz clock
+constexpr long long PAN_WAIT = 2000000;  // 20 ms of the 100 MHz clock
 // Polls of a committed panel (seconds).  Its waits end by themselves unless the device
 // is broken; a word that never came is a NaN in every later column and so in the
 // tridiagonal, where k_tri_prep turns it into a solve without finite eigenvalues.
@@ -66,26 +66,23 @@ __device__ __forceinline__ double2 xval(u64 a, u64 b) {
 }
 __device__ __forceinline__ void wait_stores() { __builtin_amdgcn_s_waitcnt(0); }
 
-// The exchange buffers of a block, carved from D.px (words); entries are complex.
-struct PanX {
-  u64 *col, *rec, *pa, *bred, *head, *yj;  // one ring slot each, see pan_slot
-};
+// One ring slot of the exchange words of a block (D.px); entries are complex.
+typedef PanParts<u64 *> PanX;
 __device__ __forceinline__ PanX pan_slot(u64 *px, int64_t n, int ring) {
-  const PanOff o = g_pan_off(n);
-  u64 *p = px + 2 * g_pan_ctrl(n) + ring * o.end;
-  return PanX{p + o.col, p + o.rec, p + o.pa, p + o.bred, p + o.head, p + o.yj};
+  return g_pan_parts(px + 2 * g_pan_ctrl(n) + ring * g_pan_ring(n), n);
 }
 
 // Every ring word to XNONE and (ctrl) the entry counters to zero, shared by the
-// nwgs workgroups of a launch in front of the panel.  Without any wait allowed the
-// panels are given up from the start: state 2, the second word of each pair.
+// nwgs workgroups of a launch in front of the panel.  Where workgroups are taken never
+// to arrive, their count (the first word of each pair) starts that much below zero and
+// the panels are given up.
 __device__ __forceinline__ void pan_clear(const Desc &D, int64_t wg, int64_t nwgs, bool ctrl) {
   if (!D.px) return;
   const int64_t c = 2 * g_pan_ctrl(D.n), w = g_pan_words(D.n);
   u64 *px = reinterpret_cast<u64 *>(D.px);
   for (int64_t k = wg * blockDim.x + threadIdx.x; k < w; k += nwgs * blockDim.x) {
     if (k >= c) px[k] = XNONE;
-    else if (ctrl) px[k] = (k & 1) && D.pan_wait == 0 ? 2 : 0;
+    else if (ctrl) px[k] = k & 1 ? 0 : u64(-int64_t(D.pan_absent));
   }
 }
 
@@ -118,7 +115,7 @@ __device__ __forceinline__ void b_panel(const Desc &D, int j0, int g0) {
       }
       const long long t0 = wall_clock64();
       while ((st = int(xld(state))) == 0) {
-        if (wall_clock64() - t0 > D.pan_wait) {
+        if (wall_clock64() - t0 > PAN_WAIT) {
           u64 e = 0;
           __hip_atomic_compare_exchange_strong(state, &e, u64(2), __ATOMIC_RELAXED,
                                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -133,7 +130,7 @@ __device__ __forceinline__ void b_panel(const Desc &D, int j0, int g0) {
   const int gb = solo ? 0 : g0, ge = solo ? G : g0 + 1;
   for (int i = 0; i < NBK; ++i) {
     const int jn = j0 + i, m0 = jn + 1;
-    const PanX X = pan_slot(px, n, i % PAN_RING), XN = pan_slot(px, n, (i + 1) % PAN_RING);
+    const PanX X = pan_slot(px, n, i & (PAN_RING - 1)), XN = pan_slot(px, n, (i + 1) & (PAN_RING - 1));
     double2 tau = {0, 0}, sc = {0, 0};
     // ================= A =================
     for (int g = gb; g < ge; ++g) {
@@ -427,7 +424,7 @@ __device__ __forceinline__ void b_panel(const Desc &D, int j0, int g0) {
       }
       // ---- every workgroup has finished column i - 1: its words back to XNONE ----
       if (i > 0) {
-        const PanX XP = pan_slot(px, n, (i - 1) % PAN_RING);
+        const PanX XP = pan_slot(px, n, (i + PAN_RING - 1) & (PAN_RING - 1));
         const int t = tid - ENT / 2;
         if (t >= 0) {
           if (t < 2 * nr) xst(XP.col + 2 * rb + t, XNONE);

@@ -41,10 +41,10 @@ namespace {
 // ---------------------------------------------------------------------------
 struct Panel {
   int n, j0, m, RW, G, ring;
-  PanOff o;
+  PanParts<int64_t> o;
   std::vector<int> tag;  // per word: 0 none, else column + 1
 
-  Panel(int n_, int j0_, int ring_) : n(n_), j0(j0_), ring(ring_), o(g_pan_off(n_)) {
+  Panel(int n_, int j0_, int ring_) : n(n_), j0(j0_), ring(ring_), o(g_pan_parts<int64_t>(0, n_)) {
     m = n - j0 - 1;
     RW = g_pan_rows(m);
     G = g_pan_wgs(m);
@@ -53,7 +53,7 @@ struct Panel {
   // word k of part [lo, hi) of the slot of column i
   size_t word(int i, int64_t lo, int64_t hi, int64_t k) const {
     if (k < 0 || lo + k >= hi) stop("word outside its part", lo + k, hi);
-    const int64_t w = 2 * g_pan_ctrl(n) + (i % ring) * o.end + lo + k;
+    const int64_t w = 2 * g_pan_ctrl(n) + (i % ring) * g_pan_ring(n) + lo + k;
     if (w < 2 * g_pan_ctrl(n) || w >= g_pan_words(n)) stop("word outside the region", w);
     return size_t(w);
   }
@@ -214,6 +214,7 @@ int layout(int64_t n, int64_t K) {
   const size_t words = size_t(g_pan_bytes(n, true));
   if (g_tail0(n) == 0) return D.px || words ? (stop("words without a panel", n), 1) : 0;
   if (reinterpret_cast<char *>(D.px) + words != buf.data() + buf.size()) stop("px is not last", n);
+  if (g_pan_parts<int64_t>(0, n).end != g_pan_ring(n)) stop("parts of a ring slot", n);
   if (words < size_t(g_pan_words(n)) * 8 || (reinterpret_cast<char *>(D.px) - buf.data()) % 8)
     stop("px too small or not aligned", n);
   for (int64_t j0 = 0; j0 < g_tail0(n); j0 += NBK) {
