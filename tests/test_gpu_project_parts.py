@@ -20,7 +20,7 @@ torch = pytest.importorskip("torch")
 # the workgroups of 17 x 17 x 1, 8^3 and 6^3 are above the line, those of 4^3 below it
 SHAPES = [("D6h", 17, 3, 7), ("D6h", 17, 2, 11), ("D6h", 17, 4, 6), ("D6h", 17, 5, 5),
           ("D6h", 17, 4, 8), ("D6h", 17, 3, 11), ("D6h", 17, 6, 6), ("D6h", 17, 6, 7),
-          ("Oh", 6, 5, 6), ("Oh", 6, 6, 7), ("Oh", 4, 5, 6), ("Oh", 7, 3, 6), ("Oh", 8, 1, 19),
+          ("Oh", 6, 5, 6), ("Oh", 6, 6, 7), ("Oh", 4, 5, 6), ("Oh", 4, 6, 7), ("D6h", 7, 1, 40), ("Oh", 7, 3, 6), ("Oh", 8, 1, 19),
           ("Oh", 8, 3, 7)]
 
 
