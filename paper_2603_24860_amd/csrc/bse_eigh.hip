@@ -2507,8 +2507,8 @@ __global__ __launch_bounds__(ENT) void k_rq_fin(Desc D) {
 
 }  // namespace
 
-// Polls of a wait inside k_sb_chase, for the solves of this host thread.
-thread_local int32_t t_chase_polls = CHASE_SPIN;
+// Waits inside k_sb_chase run out at once, for the solves of this host thread.
+thread_local bool t_chase_impatient = false;
 // Workgroups of k_panel that the device holds, for the solves and plans of this host
 // thread; negative: asked for.
 thread_local int64_t t_pan_slots = -1;
@@ -2669,7 +2669,6 @@ int32_t eigh_run_2s(int64_t n, const void *Hmu, int64_t ld, const void *Bmu, dou
                     double *pole, double *osc, void *ws, hipStream_t s, int64_t K) {
   Desc D;
   ws_layout(n, sizeof(TA) == 8, &D, (char *)ws, K, true);
-  D.chase_polls = t_chase_polls;
   D.H = Hmu;
   D.ld = ld;
   D.B = (const double2 *)Bmu;
@@ -2709,10 +2708,12 @@ int32_t eigh_run_2s(int64_t n, const void *Hmu, int64_t ld, const void *Bmu, dou
   // ---- stage 2: band -> tridiagonal ----
   if (n >= 2) {
     const dim3 g((unsigned)std::min<int64_t>(n - 1, CHASE_WGS));
-    if (K > 0)
-      BSE_LAUNCH("k_sb_chase", k_sb_chase<true>, g, dim3(BCT), 0, s, D);
+    if (t_chase_impatient)
+      BSE_LAUNCH("k_sb_chase", (k_sb_chase<false, 0>), g, dim3(BCT), 0, s, D);
+    else if (K > 0)
+      BSE_LAUNCH("k_sb_chase", (k_sb_chase<true, CHASE_SPIN>), g, dim3(BCT), 0, s, D);
     else
-      BSE_LAUNCH("k_sb_chase", k_sb_chase<false>, g, dim3(BCT), 0, s, D);
+      BSE_LAUNCH("k_sb_chase", (k_sb_chase<false, CHASE_SPIN>), g, dim3(BCT), 0, s, D);
   }
   BSE_LAUNCH("k_sb_diag", k_sb_diag, dim3((unsigned)cdiv(n, ENT)), dim3(ENT), 0, s, D);
   BSE_HIP_CHECK(hipGetLastError());
@@ -2934,9 +2935,7 @@ size_t batch_ws_bytes(int32_t nb, const int64_t *h_n, bool a_fp64, bool panels,
 
 using namespace bse;
 
-extern "C" void bse_eigh_limits(int32_t chase_polls) {
-  t_chase_polls = chase_polls < 0 ? CHASE_SPIN : chase_polls;
-}
+extern "C" void bse_eigh_chase_impatient(int32_t on) { t_chase_impatient = on != 0; }
 
 extern "C" void bse_eigh_panel_slots(int64_t slots) { t_pan_slots = slots; }
 extern "C" void bse_eigh_panel_absent(int32_t wgs) { t_pan_absent = std::max(wgs, 0); }

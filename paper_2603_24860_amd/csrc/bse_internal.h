@@ -78,9 +78,9 @@ int32_t seed_pieces(int64_t plan, SeedPieces *out);
 }  // namespace bse
 
 // For the tests of what the eigensolver does when a wait runs out; not part of the
-// interface.  Polls of one wait inside k_sb_chase, for the solves that this host thread
-// enqueues from now on; negative: the default.
-extern "C" void bse_eigh_limits(int32_t chase_polls);
+// interface.  on: the waits inside k_sb_chase run out without a poll, in the solves that
+// this host thread enqueues from now on.
+extern "C" void bse_eigh_chase_impatient(int32_t on);
 // For the tests of small devices; likewise.  Workgroups of k_panel that the device is
 // taken to hold at a time; negative: the device is asked.
 extern "C" void bse_eigh_panel_slots(int64_t slots);

@@ -301,7 +301,8 @@ __device__ __forceinline__ void b_sb_tmat(const Desc &D, int64_t j0, int nw) {
   }
 }
 
-// finished tasks of sweep i, and the next sweep to take (zeroed by k_sb_bandtail)
+// finished tasks of sweep i; the next sweep to take, and behind it whether a wait ran
+// out (zeroed by k_sb_bandtail)
 __device__ __forceinline__ int *chase_done(const Desc &D, int64_t i) {
   return reinterpret_cast<int *>(D.rfl + i * SBW);
 }
@@ -318,7 +319,7 @@ __device__ __forceinline__ void b_sb_bandtail(const Desc &D, int64_t j0) {
     D.band[j * LDB + d] = (d <= SBW && row < n) ? to_d2(A[row * D.lda + j]) : double2{0, 0};
   }
   for (int64_t i = threadIdx.x; i < n; i += ENT) *chase_done(D, i) = 0;  // of the chase
-  if (threadIdx.x == 0) *chase_next(D) = 0;
+  if (threadIdx.x == 0) chase_next(D)[0] = chase_next(D)[1] = 0;
 }
 
 // V (column major, global rows) and U = V T in the storage type of A.  A
@@ -822,8 +823,8 @@ constexpr int BCG = BCT / SBW;        // row groups g (q = g + BCG u)
 // KEEP (refinement): every reflector is also stored for the back-transformation
 constexpr int CHASE_WGS = 256;       // workgroups of the chase, at most
 // Polls of one wait (a minute).  A wait ends by itself unless the device is broken;
-// should one run out, the workgroup leaves NaN in the subdiagonal entries of its sweeps,
-// which k_tri_prep turns into a solve without finite eigenvalues, and waits no more.
+// should one run out, the second word beside the sweep counter marks the solve, whose
+// diagonal becomes NaN (k_sb_diag) and its eigenvalues with it (k_tri_prep).
 constexpr int CHASE_SPIN = 1 << 26;
 __device__ __forceinline__ double2 band_ld(const double2 *p) {
   const double *q = reinterpret_cast<const double *>(p);
@@ -835,7 +836,8 @@ __device__ __forceinline__ void band_st(double2 *p, double2 v) {
   __hip_atomic_store(q, v.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __hip_atomic_store(q + 1, v.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-template <bool KEEP>
+// SPIN: polls of one wait, at most (a constant: the loop around the poll is unrolled)
+template <bool KEEP, int SPIN>
 __global__ __launch_bounds__(BCT) void k_sb_chase(Desc D) {
   constexpr int NW = BCT / 64, NP = 8;
   static_assert(BCU == 4 && BCG == 8 && NP == 2 * NW, "k_sb_chase: two parts per wave");
@@ -847,8 +849,6 @@ __global__ __launch_bounds__(BCT) void k_sb_chase(Desc D) {
   __shared__ double2 us[SBW];           // the reflector of the previous task
   __shared__ double xsum;
   __shared__ int sweep_s, done_s;
-  __shared__ int polls_s;  // polls of a wait, -1 once one ran out (in LDS, so that the loop
-                           // over the tasks stays one of scalar branches)
   const int n = (int)D.n;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, p = tid % SBW, g = tid / SBW;
   double2 *band = D.band;
@@ -862,10 +862,7 @@ __global__ __launch_bounds__(BCT) void k_sb_chase(Desc D) {
   auto ticket = [&]() {
     return __hip_atomic_fetch_add(chase_next(D), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
-  if (tid == 0) {
-    sweep_s = ticket();
-    polls_s = D.chase_polls;
-  }
+  if (tid == 0) sweep_s = ticket();
   __syncthreads();
   // A pass of either loop begins and ends at a barrier of the workgroup or the wave:
   // where it ends in a branch of thread 0 and the next begins with one, the compiler
@@ -894,9 +891,12 @@ __global__ __launch_bounds__(BCT) void k_sb_chase(Desc D) {
           owed = false;
         }
         if (tid == 0) {
-          const int polls = polls_s;
-          for (int s = 0; s < polls && ahead() < want; ++s) __builtin_amdgcn_s_sleep(1);
-          if (ahead() < want) polls_s = -1;
+          int s = 0;
+          for (; s < SPIN && ahead() < want; ++s) __builtin_amdgcn_s_sleep(1);
+          if (s == SPIN) {  // given up: mark the solve, and wait for that sweep no more
+            chase_next(D)[1] = 1;
+            publish(i - 1, INT32_MAX);
+          }
         }
         __syncthreads();
       }
@@ -1036,7 +1036,6 @@ __global__ __launch_bounds__(BCT) void k_sb_chase(Desc D) {
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (tid == 0) {
-      if (polls_s < 0) D.e[i] = __builtin_nan("");
       publish(i, kmax + 1);
       sweep_s = ticket();
     }
@@ -1044,10 +1043,10 @@ __global__ __launch_bounds__(BCT) void k_sb_chase(Desc D) {
   }
 }
 
-// d from the band's diagonal
+// d from the band's diagonal, NaN if a wait of the chase ran out
 __global__ __launch_bounds__(ENT) void k_sb_diag(Desc D) {
   const int64_t r = int64_t(blockIdx.x) * ENT + threadIdx.x;
-  if (r < D.n) D.d[r] = D.band[r * LDB].x;
+  if (r < D.n) D.d[r] = chase_next(D)[1] ? __builtin_nan("") : D.band[r * LDB].x;
 }
 
 // ---------------------------------------------------------------------------

@@ -110,7 +110,6 @@ struct Desc {
   double2 *rfl;              // [n][SBW] its first word: finished tasks of a bulge-chasing sweep
   double2 *rtau;             // [n] its first word: the next sweep that no workgroup has taken
   double2 *sink;             // [SINK] target of the stores of masked lanes (never read)
-  int32_t chase_polls;       // polls of one wait of k_sb_chase, at most
   int32_t pan_absent;        // workgroups of each panel that are taken never to arrive
   // two-stage reduction with refinement (K > 0): every reflector of both
   // stages, for the back-transformation; null otherwise

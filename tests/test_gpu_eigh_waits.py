@@ -27,15 +27,15 @@ def _out(n):
 
 
 @contextlib.contextmanager
-def chase_polls(n):
+def impatient():
     from paper_2603_24860_amd import bse as B
-    fn = B.lib.bse_eigh_limits
+    fn = B.lib.bse_eigh_chase_impatient
     fn.restype, fn.argtypes = None, [ctypes.c_int32]
-    fn(n)
+    fn(1)
     try:
         yield
     finally:
-        fn(-1)
+        fn(0)
 
 
 @pytest.fixture
@@ -76,7 +76,7 @@ def solver(request):
 @pytest.mark.parametrize("solver", [(300, "FP32", 0, True), (700, "FP64", 0, True),
                                     (700, "FP64", 10, True), (3000, "FP32", 0, True)], indirect=True)
 def test_chase_wait_runs_out(solver):
-    with chase_polls(0):
+    with impatient():
         solver[1]()
 
 
