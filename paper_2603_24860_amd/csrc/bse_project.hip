@@ -410,7 +410,7 @@ ProjBlk proj_blk(const bse_block &b, void *Hmu, int64_t ldmu, double2 *Bmu) {
 // 20000 and 213 with 4096 workgroups), but few: the rows of many bands in turn keep
 // workgroups side by side from reading the same stretch of H (12^3, 4 + 6 bands:
 // 4.8 ms with at most 6, 5.1 with 8, 8.4 with 15, 4.9 with 1; 5.6 for a whole row
-// of H at a time through LDS; 10^3: 0.76 ms, 1.07).
+// of H at a time through LDS; 10^3: 0.76 ms, 1.07; all with the column bands whole).
 constexpr int PWGS = 8192, PBPW = 6;
 
 // Parts of the column bands (SPLIT), where the larger orbits outgrow a tile of PNT

@@ -797,7 +797,7 @@ __device__ __forceinline__ void fast_householder(double2 al, double xn2, double 
 // words to the next workgroup.  One launch per step t = 2 i + k, every task of a
 // step its own workgroup, took 6.8 us a step (2.7 us of it the launch boundary):
 // n = 10080 137 ms; one launch with six barriers of 512 threads a task 114 ms;
-// now 104 ms, 5.1 us a step.
+// now 101 ms, 5.0 us a step.
 //
 // Task (i, k) covers rows R_k = i + 1 + k SBW .. + L - 1:
 //   k > 0: the block O = A[R_k, R_{k-1}] takes the previous reflector of the
